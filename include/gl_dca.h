@@ -508,9 +508,16 @@ gl_status gl_server_destroy(gl_server *srv);
  *   d2_out   device f32 [n x k] or NULL: those squared distances, computed
  *            as sum_c (x_ic - x_jc)^2 in f32 in coordinate order
  * 1 <= d <= 4096, 1 <= k <= 32, k < n < 2^31.
- * d <= 64: one register-resident scan per query, asynchronous on `stream`; a
+ * d <= 64: asynchronous on `stream`; a
  * point with a non-finite coordinate is never chosen as a neighbour, and a
- * list that cannot be filled ends with index -1 and distance +inf.
+ * list that cannot be filled ends with index -1 and distance +inf.  Few points,
+ * d = 1, a stream under capture and a failed allocation: one scan per query,
+ * no temporary memory.  Otherwise approximate distances from the matrix
+ * cores (points split into two f16 parts, f32 accumulation), exact f32
+ * distances of each query's candidates, a proof from the rounding bounds that
+ * no other point can enter or tie, and the scan for queries without it; about
+ * n (40 d + 200) to n (40 d + 1600) bytes of stream-ordered temporaries (the
+ * more the fewer the points).
  * d > 64 (wide features, e.g. 784 pixels): the same result, found through
  * the matrix cores: <x_i, x_j> of the centred points rounded to f16 (scaled
  * by a power of two), f32 accumulation, in one fused kernel that filters

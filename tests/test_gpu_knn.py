@@ -108,6 +108,76 @@ def test_knn_rejects_bad_sizes():
         gl.knn(torch.zeros((10, 4097), device=DEV), 3)
 
 
+# The matrix-core path (d <= 64): edges of its dispatch.  Coordinates are small
+# integers, so every distance is an exact f32 integer and the lists, ties to the
+# lower index included, must equal the oracle's bit for bit.
+#   d 4|5, 10|11, 15|16, 20|21, 31|32, 42|43: one k-step more;  k 4|5, 8|9, 12|13,
+#   16|17, 20|21, 28|29: a longer list;  n: below, at and beyond a tile and a
+#   workgroup of queries, one and several point segments.
+@pytest.mark.parametrize("n,d,k,span", [
+    (6000, 2, 4, 60), (6001, 4, 5, 12), (5856, 5, 8, 9), (5857, 10, 9, 6), (6015, 11, 12, 6), (6017, 15, 13, 6),
+    (5000, 16, 16, 5), (4000, 20, 17, 5), (4001, 21, 20, 5), (3999, 31, 21, 4), (3000, 32, 28, 4), (3001, 42, 29, 4),
+    (3002, 43, 32, 4), (2500, 64, 31, 4), (20000, 3, 10, 40), (65600, 3, 7, 200)])
+def test_knn_matrix_path_exact(n, d, k, span):
+    rng = np.random.default_rng(n + d)
+    x = rng.integers(0, span, (n, d)).astype(np.float32)
+    say(f"knn n={n} d={d} k={k} integers below {span}")
+    idx, d2 = gl.knn(torch.from_numpy(x).to(DEV), k)
+    rows = np.arange(n) if n <= 6100 else np.concatenate([np.arange(40), rng.choice(n, 400, replace=False), np.arange(n - 40, n)])
+    oi, od = knn_oracle.knn(x.astype(np.float64), k, rows=rows)
+    assert np.array_equal(idx.cpu().numpy()[rows], oi)
+    assert np.array_equal(d2.cpu().numpy()[rows].astype(np.float64), od)
+
+
+@pytest.mark.parametrize("n,shift,outlier", [(7000, 0.0, 0.0), (9000, 0.0, 0.0), (7000, 4096.0, 0.0), (7000, 0.0, 65536.0)])
+def test_knn_every_query_rescanned(n, shift, outlier):
+    """27 distinct places: every list is full of ties, so no query has a proof
+    and all are scanned (one, and four, queries per wavefront); far from the
+    origin, and with a point that sets the scale alone."""
+    rng = np.random.default_rng(n)
+    x = (rng.integers(0, 3, (n, 3)) + shift).astype(np.float32)
+    x[5] += outlier
+    k = 20
+    idx, d2 = gl.knn(torch.from_numpy(x).to(DEV), k)
+    rows = np.delete(np.arange(n), 5)  # the outlier's own distances exceed f32's integers
+    oi, od = knn_oracle.knn(x.astype(np.float64), k, rows=rows)
+    assert np.array_equal(idx.cpu().numpy()[rows], oi)
+    assert np.array_equal(d2.cpu().numpy()[rows].astype(np.float64), od)
+
+
+def test_knn_matrix_path_nonfinite_and_constant():
+    n, k = 6000, 6
+    x = np.random.default_rng(3).integers(0, 40, (n, 3)).astype(np.float32)
+    x[17, 1], x[99, 0], x[1234, 2] = np.nan, np.inf, -np.inf
+    ok = np.isfinite(x).all(1)
+    idx, d2 = (t.cpu().numpy() for t in gl.knn(torch.from_numpy(x).to(DEV), k))
+    back = np.flatnonzero(ok)
+    oi, od = knn_oracle.knn(x[ok].astype(np.float64), k)
+    assert np.array_equal(idx[ok], back[oi]) and np.array_equal(d2[ok].astype(np.float64), od)
+    assert np.all(idx[~ok] == -1) and np.all(np.isinf(d2[~ok]))
+    # all points alike: the lowest other indices, at distance 0
+    idx, d2 = (t.cpu().numpy() for t in gl.knn(torch.full((n, 3), 2.5, device=DEV), k))
+    assert np.all(d2 == 0.0)
+    assert np.array_equal(idx[100], np.arange(k)) and np.array_equal(idx[2], [0, 1, 3, 4, 5, 6])
+
+
+def test_knn_under_capture():
+    """A captured call (scanned: it allocates nothing) on new contents at every replay."""
+    n, d, k = 6500, 4, 8
+    rng = np.random.default_rng(7)
+    x = torch.zeros((n, d), device=DEV)
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        idx, d2 = gl.knn(x, k)
+    for _ in range(3):
+        xi = rng.integers(0, 12, (n, d)).astype(np.float32)
+        x.copy_(torch.from_numpy(xi))
+        g.replay()
+        torch.cuda.synchronize()
+        ei, ed = gl.knn(x, k)
+        assert torch.equal(idx, ei) and torch.equal(d2, ed)
+
+
 # ---------------------------------------------------------------------------
 # gl_knn_graph: union-symmetric graph with local-scaling weights
 # ---------------------------------------------------------------------------
