@@ -2,6 +2,7 @@
 // Laplacian product, power method, the preconditioned DCA solve and labelling.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
@@ -121,6 +122,27 @@ gl::RowLaunch gl::operator_rows(const gl_operator* op) {
     r.rows_per_block = (int64_t)(gl::kBlock >> op->log2G) * op->tiles;
     r.grid = (op->n + r.rows_per_block - 1) / r.rows_per_block;
     return r;
+}
+
+hipError_t gl::check_diagonal(const void* dd, bool f64, int64_t n, void* scratch, hipStream_t s, double& largest,
+                              bool& bad) {
+    unsigned long long h[2] = {0, 0};
+    hipError_t e = hipMemcpyAsync(scratch, h, sizeof(h), hipMemcpyHostToDevice, s);
+    const dim3 grid((unsigned)std::min<int64_t>((n + 255) / 256, 1024)), block(256);
+    if (e == hipSuccess) {
+        if (f64)
+            hipLaunchKernelGGL(gl::diagonal_kernel<double>, grid, block, 0, s, n, (const double*)dd,
+                               (unsigned long long*)scratch);
+        else
+            hipLaunchKernelGGL(gl::diagonal_kernel<float>, grid, block, 0, s, n, (const float*)dd,
+                               (unsigned long long*)scratch);
+        e = hipGetLastError();
+    }
+    if (e == hipSuccess) e = hipMemcpyAsync(h, scratch, sizeof(h), hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    std::memcpy(&largest, &h[0], 8);
+    bad = h[1] != 0;
+    return e;
 }
 
 namespace {
@@ -246,8 +268,7 @@ gl_status check_params(const gl_params* p) {
 
 template <typename TIN, typename TOUT, typename OffT>
 void launch_normalize(gl_operator* op, const gl_graph* g, hipStream_t s) {
-    const unsigned grid = (unsigned)((op->n + 1 + 255) / 256);
-    hipLaunchKernelGGL((gl::normalize_kernel<TIN, TOUT, OffT>), dim3(grid), dim3(256), 0, s, op->n, g->row_ptr,
+    hipLaunchKernelGGL((gl::normalize_kernel<TIN, TOUT, OffT>), dim3(gl::row_grid(op->n + 1)), dim3(256), 0, s, op->n, g->row_ptr,
                        g->col_idx, static_cast<const TIN*>(g->weight), op->degree, static_cast<OffT*>(op->rp),
                        op->col, static_cast<TOUT*>(op->w), op->lap == GL_LAP_UNNORMALIZED ? 1 : 0);
 }
@@ -324,7 +345,7 @@ hipError_t launch_grid_rowsum(gl_operator* op, const gl_graph* g, hipStream_t s)
     return hipGetLastError();
 }
 
-gl_status finish_unnormalized(gl_operator* op, hipStream_t s, const gl_graph* g = nullptr) {
+gl_status finish_unnormalized(gl_operator* op, void* scratch, hipStream_t s, const gl_graph* g = nullptr) {
     if (op->lap != GL_LAP_UNNORMALIZED) return GL_OK;
     const size_t es = op->store_w == GL_F64 ? 8 : 4;
     if (hipMalloc(&op->dd, (size_t)op->n * es) != hipSuccess)
@@ -346,16 +367,12 @@ gl_status finish_unnormalized(gl_operator* op, hipStream_t s, const gl_graph* g 
             default: e = launch_rowsum<gl::f16, float>(op, s); break;
         }
     }
-    std::vector<char> h((size_t)op->n * es);
-    if (e == hipSuccess) e = hipMemcpyAsync(h.data(), op->dd, h.size(), hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) return fail(GL_E_HIP, std::string("operator diagonal: ") + hipGetErrorString(e));
     double m = 0.0;
-    for (int64_t i = 0; i < op->n; ++i) {
-        const double v = es == 8 ? ((const double*)h.data())[i] : (double)((const float*)h.data())[i];
-        if (!(v > 0.0) || !std::isfinite(v)) return fail(GL_E_BAD_GRAPH, "a stored row sums to a non-positive degree");
-        m = v > m ? v : m;
-    }
+    bool bad = false;
+    e = gl::check_diagonal(op->dd, es == 8, op->n, scratch, s, m, bad);
+    if (e != hipSuccess) return fail(GL_E_HIP, std::string("operator diagonal: ") + hipGetErrorString(e));
+    if (bad) return fail(GL_E_BAD_GRAPH, "a stored row sums to a non-positive degree");
     op->dmax = m;
     return GL_OK;
 }
@@ -524,18 +541,13 @@ gl_status gl_operator_create(const gl_graph* g, gl_dtype store_w, void* stream, 
     op->tiles = geom.tiles;
     op->remap = 1;
 
-    void* scratch = nullptr;  // [int32 flags][pad][u64 first_bad]
+    void* scratch = nullptr;  // GraphCheck, then the grid layout's checks
     if (hipMalloc((void**)&op->degree, (size_t)g->n * 8) != hipSuccess || hipMalloc(&scratch, 64) != hipSuccess) {
         (void)hipFree(scratch);
         free_op(op);
         return fail(GL_E_NOMEM, "device allocation for the operator failed");
     }
-    int32_t* d_flags = (int32_t*)scratch;
-    unsigned long long* d_first = (unsigned long long*)((char*)scratch + 8);
-    struct {
-        int32_t flags, pad;
-        unsigned long long first;
-    } init = {0, 0, ~0ull};
+    gl::GraphCheck check = {0, 0, ~0ull, ~0ull, 0, 0};
     int64_t ends[2] = {-1, -1};
     int32_t* d_src = nullptr;
     auto cleanup_fail = [&](gl_status st, const std::string& m) {
@@ -545,7 +557,7 @@ gl_status gl_operator_create(const gl_graph* g, gl_dtype store_w, void* stream, 
         free_op(op);
         return fail(st, m);
     };
-    if (hipMemcpyAsync(scratch, &init, sizeof(init), hipMemcpyHostToDevice, s) != hipSuccess ||
+    if (hipMemcpyAsync(scratch, &check, sizeof(check), hipMemcpyHostToDevice, s) != hipSuccess ||
         hipMemcpyAsync(&ends[0], g->row_ptr, 8, hipMemcpyDeviceToHost, s) != hipSuccess ||
         hipMemcpyAsync(&ends[1], g->row_ptr + g->n, 8, hipMemcpyDeviceToHost, s) != hipSuccess ||
         hipStreamSynchronize(s) != hipSuccess)
@@ -554,30 +566,23 @@ gl_status gl_operator_create(const gl_graph* g, gl_dtype store_w, void* stream, 
         return cleanup_fail(GL_E_BAD_GRAPH, "bad graph: row_ptr[0] must be 0 and row_ptr[n] must equal nnz");
 
     const unsigned grid = (unsigned)((g->n + 255) / 256);
+    const int64_t heavy_min = gl::heavy_threshold(op->G);
     if (g->weight_dtype == GL_F64) {
-        hipLaunchKernelGGL(gl::validate_kernel<double>, dim3(grid), dim3(256), 0, s, g->n, g->nnz, g->row_ptr,
-                           g->col_idx, (const double*)g->weight, d_flags, d_first);
+        hipLaunchKernelGGL(gl::validate_kernel<double>, dim3(gl::row_grid(g->n)), dim3(256), 0, s, g->n, g->nnz,
+                           g->row_ptr, g->col_idx, (const double*)g->weight, heavy_min, op->degree,
+                           (gl::GraphCheck*)scratch);
     } else {
-        hipLaunchKernelGGL(gl::validate_kernel<float>, dim3(grid), dim3(256), 0, s, g->n, g->nnz, g->row_ptr,
-                           g->col_idx, (const float*)g->weight, d_flags, d_first);
+        hipLaunchKernelGGL(gl::validate_kernel<float>, dim3(gl::row_grid(g->n)), dim3(256), 0, s, g->n, g->nnz,
+                           g->row_ptr, g->col_idx, (const float*)g->weight, heavy_min, op->degree,
+                           (gl::GraphCheck*)scratch);
     }
     if (hipGetLastError() != hipSuccess) return cleanup_fail(GL_E_HIP, "validate launch failed");
-    if (hipMemcpyAsync(&init, scratch, sizeof(init), hipMemcpyDeviceToHost, s) != hipSuccess ||
+    if (hipMemcpyAsync(&check, scratch, sizeof(check), hipMemcpyDeviceToHost, s) != hipSuccess ||
         hipStreamSynchronize(s) != hipSuccess)
         return cleanup_fail(GL_E_HIP, "graph validation failed");
-    if (init.flags) return cleanup_fail(GL_E_BAD_GRAPH, bad_graph_message(init.flags, init.first));
-
-    if (g->weight_dtype == GL_F64) {
-        hipLaunchKernelGGL(gl::degree_kernel<double>, dim3(grid), dim3(256), 0, s, g->n, g->row_ptr,
-                           (const double*)g->weight, op->degree, d_flags, d_first);
-    } else {
-        hipLaunchKernelGGL(gl::degree_kernel<float>, dim3(grid), dim3(256), 0, s, g->n, g->row_ptr,
-                           (const float*)g->weight, op->degree, d_flags, d_first);
-    }
-    if (hipMemcpyAsync(&init, scratch, sizeof(init), hipMemcpyDeviceToHost, s) != hipSuccess ||
-        hipStreamSynchronize(s) != hipSuccess)
-        return cleanup_fail(GL_E_HIP, "degree computation failed");
-    if (init.flags) return cleanup_fail(GL_E_BAD_GRAPH, bad_graph_message(init.flags, init.first));
+    if (check.flags) return cleanup_fail(GL_E_BAD_GRAPH, bad_graph_message(check.flags, check.first));
+    if (check.degree_flags)
+        return cleanup_fail(GL_E_BAD_GRAPH, bad_graph_message(check.degree_flags, check.first_degree));
 
     const size_t sw = dtype_size(store_w);
     if (grid_req) {
@@ -661,7 +666,7 @@ gl_status gl_operator_create(const gl_graph* g, gl_dtype store_w, void* stream, 
             return grid_fail(GL_E_HIP, "grid layout: chunk emission failed");
         (void)hipFree(seg);
         seg = nullptr;
-        const gl_status su = finish_unnormalized(op, s, g);
+        const gl_status su = finish_unnormalized(op, scratch, s, g);
         if (su != GL_OK) {
             const std::string m = gl_last_error();
             return cleanup_fail(su, m);
@@ -681,13 +686,13 @@ gl_status gl_operator_create(const gl_graph* g, gl_dtype store_w, void* stream, 
         else launch_normalize_out<float>(op, g, s);
         if (hipGetLastError() != hipSuccess || hipStreamSynchronize(s) != hipSuccess)
             return cleanup_fail(GL_E_HIP, "weight normalization failed");
-        {
+        if (check.heavy > 0) {  // only then are the row offsets looked through on the host
             std::vector<int64_t> h_rp(g->n + 1);
             if (hipMemcpy(h_rp.data(), g->row_ptr, h_rp.size() * 8, hipMemcpyDeviceToHost) != hipSuccess ||
                 set_heavy_rows(op, h_rp.data(), s) != hipSuccess)
                 return cleanup_fail(GL_E_HIP, "heavy-row list failed");
         }
-        const gl_status su = finish_unnormalized(op, s);
+        const gl_status su = finish_unnormalized(op, scratch, s);
         if (su != GL_OK) {
             const std::string m = gl_last_error();
             return cleanup_fail(su, m);
@@ -747,13 +752,13 @@ gl_status gl_operator_create(const gl_graph* g, gl_dtype store_w, void* stream, 
     const bool fill_ok = hipGetLastError() == hipSuccess && hipStreamSynchronize(s) == hipSuccess;
     (void)hipFree(d_pos_of);
     if (!fill_ok) return cleanup_fail(GL_E_HIP, "weight normalization failed");
-    if (op->layout == gl::LAYOUT_DIRECT) {
+    if (op->layout == gl::LAYOUT_DIRECT && check.heavy > 0) {
         std::vector<int32_t> h_srp(g->n + 1);
         if (hipMemcpy(h_srp.data(), op->rp, h_srp.size() * 4, hipMemcpyDeviceToHost) != hipSuccess ||
             set_heavy_rows(op, h_srp.data(), s) != hipSuccess)
             return cleanup_fail(GL_E_HIP, "heavy-row list failed");
     }
-    const gl_status su = finish_unnormalized(op, s);
+    const gl_status su = finish_unnormalized(op, scratch, s);
     if (su != GL_OK) {
         const std::string m = gl_last_error();
         return cleanup_fail(su, m);

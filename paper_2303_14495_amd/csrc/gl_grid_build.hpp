@@ -21,8 +21,7 @@ namespace gl {
 static __global__ void grid_count_kernel(int64_t n, int32_t width, const int64_t* __restrict__ rp,
                                          const int32_t* __restrict__ col, uint8_t* __restrict__ cnt,
                                          int32_t* flags, unsigned long long* first, int32_t* mincnt) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
+    const int64_t at = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, i = min(at, n - 1);
     // n < 2^31 and width < 2^24: 32-bit arithmetic
     const int32_t yi = (int32_t)i / width, xi = (int32_t)i - yi * width;
     const int64_t beg = rp[i], end = rp[i + 1];
@@ -36,9 +35,11 @@ static __global__ void grid_count_kernel(int64_t n, int32_t width, const int64_t
         atomicMin(first, (unsigned long long)i);
     }
     // at most 224 distinct window cells (columns are strictly increasing)
-    const int c = (int)((end - beg + kGridChunk - 1) / kGridChunk);
-    cnt[i] = (uint8_t)(c < 255 ? c : 255);
-    atomicMin(mincnt, c);
+    int c = (int)((end - beg + kGridChunk - 1) / kGridChunk);
+    if (at < n) cnt[i] = (uint8_t)(c < 255 ? c : 255);
+    // one atomic per wavefront (lanes beyond n repeat the last pixel)
+    for (int off = 32; off > 0; off >>= 1) c = min(c, __shfl_xor(c, off, 64));
+    if ((threadIdx.x & 63) == 0) atomicMin(mincnt, c);
 }
 
 // Row segment s (tile-major: s = tile * 8 + row in tile): its chunks beyond

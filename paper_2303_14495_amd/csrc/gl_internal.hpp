@@ -118,6 +118,12 @@ inline int64_t sweep_grid(const RowLaunch& r) {
     return r.grid + (r.layout == LAYOUT_DIRECT ? ((int64_t)r.nheavy + 7) / 8 * 8 : 0);
 }
 
+// Whether some entry of the diagonal dd (double or float, n of them) is not
+// positive and finite, and its largest entry; scratch: 16 device bytes.
+// Synchronises `s`.
+hipError_t check_diagonal(const void* dd, bool f64, int64_t n, void* scratch, hipStream_t s, double& largest,
+                          bool& bad);
+
 // Power-method pass on the window layout (see gl::window_power_kernel); part:
 // window_part_bytes(op, 1, 4) bytes.
 hipError_t launch_window_power(const gl_operator* op, const float* x, float* y, int mode, const float* scale,

@@ -203,82 +203,130 @@ enum : int32_t {
     BAD_DEGREE = 64
 };
 
-template <typename TIN>
-__global__ void validate_kernel(int64_t n, int64_t nnz, const int64_t* __restrict__ rp,
-                                const int32_t* __restrict__ col, const TIN* __restrict__ w,
-                                int32_t* flags, unsigned long long* first_bad) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    int32_t f = 0;
-    const int64_t beg = rp[i], end = rp[i + 1];
-    if (beg < 0 || end < beg || end > nnz) {
-        f |= BAD_ROWPTR;
-    } else {
-        int64_t prev = -1;
-        for (int64_t p = beg; p < end; ++p) {
-            const int64_t j = col[p];
-            if (j < 0 || j >= n) {
-                f |= BAD_COL_RANGE;
-                break;
-            }
-            if (j <= prev) f |= BAD_COL_ORDER;
-            prev = j;
-            if (j == i) f |= BAD_SELF_LOOP;
-            const double wv = (double)w[p];
-            if (!(wv > 0.0) || !(wv <= 1.7976931348623157e308)) f |= BAD_WEIGHT;
-            // symmetry: find i in row j by binary search and compare the weight bits
-            const int64_t jb = rp[j], je = rp[j + 1];
-            if (jb < 0 || je < jb || je > nnz) {
-                f |= BAD_ROWPTR;
-                continue;
-            }
-            int64_t lo = jb, hi = je;
-            while (lo < hi) {
-                const int64_t mid = (lo + hi) >> 1;
-                if (col[mid] < i) lo = mid + 1; else hi = mid;
-            }
-            if (lo >= je || col[lo] != i || !(w[lo] == w[p])) f |= BAD_ASYMMETRIC;
-        }
-    }
-    if (f) {
-        atomicOr(flags, f);
-        atomicMin(first_bad, (unsigned long long)i);
-    }
+constexpr int kRowLanes = 16;  // lanes per row of the construction kernels
+
+template <typename T, typename OP> __device__ __forceinline__ T row_reduce(T v, OP op) {
+#pragma unroll
+    for (int off = kRowLanes / 2; off > 0; off >>= 1) v = op(v, __shfl_xor(v, off, kRowLanes));
+    return v;
 }
 
+// What the construction finds out about a graph (zeroed, the firsts all ones).
+struct GraphCheck {
+    int32_t flags;         // defects of the structure or the weights
+    int32_t degree_flags;  // BAD_DEGREE (meaningful when flags == 0)
+    unsigned long long first, first_degree;  // first rows with them
+    int32_t heavy;         // rows longer than heavy_min
+    int32_t pad;
+};
+
+// The defects of row i among its entries before `stop` (the row ends at the
+// first column out of range, which is a defect itself), for one of the row's
+// kRowLanes lanes; *range: that lane's first column out of range.
 template <typename TIN>
-__global__ void degree_kernel(int64_t n, const int64_t* __restrict__ rp, const TIN* __restrict__ w,
-                              double* __restrict__ d, int32_t* flags, unsigned long long* first_bad) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
+__device__ __forceinline__ int32_t check_entries(int64_t i, int64_t n, int64_t nnz, const int64_t* __restrict__ rp,
+                                                 const int32_t* __restrict__ col, const TIN* __restrict__ w,
+                                                 int64_t beg, int64_t stop, int q, int64_t& range, double& sum) {
+    int32_t f = 0;
+    for (int64_t p = beg + q; p < stop; p += kRowLanes) {
+        const int64_t j = col[p];
+        if (j < 0 || j >= n) {
+            f |= BAD_COL_RANGE;
+            range = p;
+            break;
+        }
+        if (p > beg && j <= (int64_t)col[p - 1]) f |= BAD_COL_ORDER;
+        if (j == i) f |= BAD_SELF_LOOP;
+        const TIN wp = w[p];
+        const double wv = (double)wp;
+        if (!(wv > 0.0) || !(wv <= 1.7976931348623157e308)) f |= BAD_WEIGHT;
+        sum += wv;
+        // symmetry: find i in row j by binary search and compare the weight bits
+        const int64_t jb = rp[j], je = rp[j + 1];
+        if (jb < 0 || je < jb || je > nnz) {
+            f |= BAD_ROWPTR;
+            continue;
+        }
+        int64_t lo = jb, hi = je;
+        while (lo < hi) {
+            const int64_t mid = (lo + hi) >> 1;
+            if (col[mid] < i) lo = mid + 1; else hi = mid;
+        }
+        if (lo >= je || col[lo] != i || !(w[lo] == wp)) f |= BAD_ASYMMETRIC;
+    }
+    return f;
+}
+
+// Checks of the CSR graph and its degrees d_i = sum of row i's weights (double,
+// every kRowLanes-th entry in turn, then a butterfly).  kRowLanes lanes per row:
+// a lane per row walked its 20-odd entries alone, a dependent chain of about
+// five loads each, and the degrees were a second pass (535 + 59 us for the 5.4 M
+// entries of a 453 x 601 image's graph, 129 us so; 327 + 24 us and 195 us for the
+// 4 M of 262 144 points' kNN graph).
+template <typename TIN>
+__global__ __launch_bounds__(256) void validate_kernel(int64_t n, int64_t nnz, const int64_t* __restrict__ rp,
+                                                       const int32_t* __restrict__ col, const TIN* __restrict__ w,
+                                                       int64_t heavy_min, double* __restrict__ d,
+                                                       GraphCheck* __restrict__ check) {
+    const int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kRowLanes;
+    const int q = threadIdx.x % kRowLanes;
+    if (i >= n) return;  // whole groups
+    const int64_t beg = rp[i], end = rp[i + 1];
+    int32_t f = 0;
     double s = 0.0;
-    for (int64_t p = rp[i]; p < rp[i + 1]; ++p) s += (double)w[p];
+    if (beg < 0 || end < beg || end > nnz) {
+        f = BAD_ROWPTR;
+    } else {
+        int64_t range = INT64_MAX;
+        f = check_entries(i, n, nnz, rp, col, w, beg, end, q, range, s);
+        const int64_t stop = row_reduce(range, [](int64_t a, int64_t b) { return a < b ? a : b; });
+        if (stop != INT64_MAX) {
+            s = 0.0;
+            f = check_entries(i, n, nnz, rp, col, w, beg, stop, q, range, s) | BAD_COL_RANGE;
+        }
+        f = row_reduce(f, [](int32_t a, int32_t b) { return a | b; });
+        s = row_reduce(s, [](double a, double b) { return a + b; });
+        if (q == 0 && end - beg > heavy_min) atomicAdd(&check->heavy, 1);
+    }
+    if (q != 0) return;
     d[i] = s;
-    if (!(s > 0.0) || !(s <= 1.7976931348623157e308)) {
-        atomicOr(flags, (int32_t)BAD_DEGREE);
-        atomicMin(first_bad, (unsigned long long)i);
+    if (f) {
+        atomicOr(&check->flags, f);
+        atomicMin(&check->first, (unsigned long long)i);
+    } else if (!(s > 0.0) || !(s <= 1.7976931348623157e308)) {
+        atomicOr(&check->degree_flags, (int32_t)BAD_DEGREE);
+        atomicMin(&check->first_degree, (unsigned long long)i);
     }
 }
 
 // what_ij = w_ij / (sqrt(d_i) sqrt(d_j)) in double, rounded once to TOUT; the index
 // arrays are copied (row offsets narrowed to OffT) in the same pass.
 // raw != 0 (unnormalized L = D - W): w_ij itself, rounded once to TOUT.
+// kRowLanes lanes per row, so that the arrays are read and written in runs (4 M
+// entries to bf16: 190 us with a lane per row, 35 us so).
 template <typename TIN, typename TOUT, typename OffT>
-__global__ void normalize_kernel(int64_t n, const int64_t* __restrict__ rp, const int32_t* __restrict__ col,
-                                 const TIN* __restrict__ w, const double* __restrict__ d,
-                                 OffT* __restrict__ rp_out, int32_t* __restrict__ col_out,
-                                 TOUT* __restrict__ w_out, int32_t raw) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+__global__ __launch_bounds__(256) void normalize_kernel(int64_t n, const int64_t* __restrict__ rp,
+                                                        const int32_t* __restrict__ col, const TIN* __restrict__ w,
+                                                        const double* __restrict__ d, OffT* __restrict__ rp_out,
+                                                        int32_t* __restrict__ col_out, TOUT* __restrict__ w_out,
+                                                        int32_t raw) {
+    const int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kRowLanes;
+    const int q = threadIdx.x % kRowLanes;
     if (i > n) return;
-    rp_out[i] = (OffT)rp[i];
+    const int64_t beg = rp[i];
+    if (q == 0) rp_out[i] = (OffT)beg;
     if (i == n) return;
-    const double di = d[i];
-    for (int64_t p = rp[i]; p < rp[i + 1]; ++p) {
+    const int64_t end = rp[i + 1];
+    const double ri = raw ? 1.0 : sqrt(d[i]);
+    for (int64_t p = beg + q; p < end; p += kRowLanes) {
         const int32_t j = col[p];
         col_out[p] = j;
-        w_out[p] = store_as<TOUT>::from(raw ? (double)w[p] : (double)w[p] / (sqrt(di) * sqrt(d[j])));
+        w_out[p] = store_as<TOUT>::from(raw ? (double)w[p] : (double)w[p] / (ri * sqrt(d[j])));
     }
 }
+
+// Workgroups of 256 threads for `rows` rows of kRowLanes lanes.
+inline unsigned row_grid(int64_t rows) { return (unsigned)((rows * kRowLanes + 255) / 256); }
 
 // Diagonal of the unnormalized operator as stored: dd_p = sum of the row's
 // stored (rounded) weights, summed in double in storage order, rounded to A.
@@ -291,6 +339,25 @@ __global__ void rowsum_kernel(int64_t n, const OffT* __restrict__ rp, const TW* 
     double s = 0.0;
     for (int64_t p = rp[i]; p < rp[i + 1]; ++p) s += cvt<double>(w[p]);
     dd[i] = (A)s;
+}
+
+// Largest entry of a diagonal as the bits of a non-negative double (monotone
+// as unsigned) in out[0], and out[1] != 0 where an entry is not positive and finite.
+template <typename A>
+__global__ __launch_bounds__(256) void diagonal_kernel(int64_t n, const A* __restrict__ dd, unsigned long long* out) {
+    double m = 0.0;
+    bool bad = false;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+        const double v = (double)dd[i];
+        if (!(v > 0.0) || !(v <= 1.7976931348623157e308)) bad = true;
+        else m = v > m ? v : m;
+    }
+    for (int off = 32; off > 0; off >>= 1) m = fmax(m, __shfl_xor(m, off, 64));
+    const bool any = __ballot(bad) != 0;
+    if ((threadIdx.x & 63) == 0) {
+        atomicMax(out, (unsigned long long)__double_as_longlong(m));
+        if (any) atomicMax(out + 1, 1ull);
+    }
 }
 
 }  // namespace gl

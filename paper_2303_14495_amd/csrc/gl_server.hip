@@ -400,10 +400,7 @@ struct gl_server {
         s.d_flags = (int32_t*)take(held, 256);
 
         hipStream_t st = s_load;
-        struct {
-            int32_t flags, pad;
-            unsigned long long first;
-        } fl = {0, 0, ~0ull};
+        gl::GraphCheck fl = {0, 0, ~0ull, ~0ull, 0, 0};
         hipError_t e = hipMemcpyAsync(s.d_rp64, s.h_rp, (s.n + 1) * 8, hipMemcpyHostToDevice, st);
         if (e == hipSuccess) e = hipMemcpyAsync(s.d_colin, s.h_col, s.nnz * 4, hipMemcpyHostToDevice, st);
         if (e == hipSuccess) e = hipMemcpyAsync(s.d_win, s.h_w, s.nnz * 8, hipMemcpyHostToDevice, st);
@@ -416,11 +413,8 @@ struct gl_server {
             set_fatal(std::string("server copy: ") + hipGetErrorString(e));
             return GL_E_HIP;
         }
-        // Validation, degrees and normalisation run one after another with a
-        // host check in between: the later kernels trust the row offsets and
-        // columns, so they only run on a graph that passed the previous step.
-        const unsigned grid = (unsigned)((s.n + 255) / 256);
-        unsigned long long* first = (unsigned long long*)((char*)s.d_flags + 8);
+        // Normalisation trusts the row offsets and columns: it only runs on a
+        // graph that has passed the checks.
         auto read_flags = [&]() {
             hipError_t e2 = hipGetLastError();
             if (e2 == hipSuccess) e2 = hipMemcpyAsync(&fl, s.d_flags, sizeof(fl), hipMemcpyDeviceToHost, st);
@@ -444,23 +438,19 @@ struct gl_server {
             s.u0.clear();
             s.u0.shrink_to_fit();
         };
-        hipLaunchKernelGGL(gl::validate_kernel<double>, dim3(grid), dim3(256), 0, st, s.n, s.nnz, s.d_rp64,
-                           s.d_colin, s.d_win, s.d_flags, first);
+        hipLaunchKernelGGL(gl::validate_kernel<double>, dim3(gl::row_grid(s.n)), dim3(256), 0, st, s.n, s.nnz,
+                           s.d_rp64, s.d_colin, s.d_win, gl::heavy_threshold(s.geom.G), s.d_deg,
+                           (gl::GraphCheck*)s.d_flags);
         e = read_flags();
-        if (e == hipSuccess && fl.flags == 0) {
-            hipLaunchKernelGGL(gl::degree_kernel<double>, dim3(grid), dim3(256), 0, st, s.n, s.d_rp64, s.d_win,
-                               s.d_deg, s.d_flags, first);
-            e = read_flags();
-        }
         if (e != hipSuccess) {
             set_fatal(std::string("server validation: ") + hipGetErrorString(e));
             return GL_E_HIP;
         }
-        if (fl.flags) {
+        if (fl.flags || fl.degree_flags) {
             drop_host_copies();
             return GL_E_BAD_GRAPH;
         }
-        const unsigned grid1 = (unsigned)((s.n + 1 + 255) / 256);
+        const unsigned grid1 = gl::row_grid(s.n + 1);
         switch (cfg.store_w) {
             case GL_F32:
                 hipLaunchKernelGGL((gl::normalize_kernel<double, float, int32_t>), dim3(grid1), dim3(256), 0, st, s.n,
