@@ -14,7 +14,7 @@ namespace gl {
 namespace {
 
 struct WinAlpha {
-    double a[(2 * kWinMaxRp + 1) * (2 * kWinMaxRp + 1)];  // row-major over the patch offsets
+    double g[kWinMaxRp + 1];  // normalised patch weights by distance from the centre: alpha_(a,b) = g(|a|) g(|b|)
 };
 
 // Colours with a border of rp pixels replicated from the nearest edge pixel,
@@ -36,95 +36,198 @@ __global__ void window_pad_kernel(const float* __restrict__ img, int32_t h, int3
     J[i] = v;
 }
 
-// Raw weights in double, one block per (tile, offset m of the first half of
-// the scan order); the weight of the pair (p, q = p + o_m) is written to p's
-// slot m and to q's slot M - 1 - m (offset -o_m), so the stored W is
-// symmetric bit for bit.  raw[(tile * M + m) * 256 + lane], zero-initialised.
-__global__ __launch_bounds__(256) void window_raw_kernel(const float4* __restrict__ J, int32_t h, int32_t w,
-                                                         int32_t r, int32_t rp, int32_t tiles_x, int32_t M,
-                                                         WinAlpha al, double inv_s2, double* __restrict__ raw) {
-    const int64_t b = blockIdx.x;
-    const int m = blockIdx.y;  // < M / 2: the cell index of the scan equals m
-    const int side = 2 * r + 1;
-    const int dy = m / side - r, dx = m - (m / side) * side - r;
-    const int ty = (int)(b / tiles_x), tx = (int)(b - (int64_t)ty * tiles_x);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int x = tx * kWinTX + lane, y = ty * kWinTY + wave;
-    const int qx = x + dx, qy = y + dy;
-    if (x >= w || y >= h || qx < 0 || qx >= w || qy < 0 || qy >= h) return;
-    const int64_t Jw = (int64_t)w + 2 * rp;
-    const int pw = 2 * rp + 1;
-    double s = 0.0;
-    for (int a = 0; a < pw; ++a) {
-        const float4* rowp = J + (int64_t)(y + a) * Jw + x;
-        const float4* rowq = J + (int64_t)(qy + a) * Jw + qx;
-        for (int c = 0; c < pw; ++c) {
-            const float4 cp = rowp[c], cq = rowq[c];
-            const double d0 = (double)cp.x - (double)cq.x, d1 = (double)cp.y - (double)cq.y;
-            const double d2 = (double)cp.z - (double)cq.z, d3 = (double)cp.w - (double)cq.w;
-            s += al.a[a * pw + c] * (((d0 * d0 + d1 * d1) + d2 * d2) + d3 * d3);
-        }
+__device__ __forceinline__ double lane_shift(double x, bool up) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, x);
+    int lo = (int)(uint32_t)u, hi = (int)(uint32_t)(u >> 32);
+    if (up) {
+        lo = __builtin_amdgcn_update_dpp(0, lo, 0x138, 0xf, 0xf, false);  // wave_shr:1
+        hi = __builtin_amdgcn_update_dpp(0, hi, 0x138, 0xf, 0xf, false);
+    } else {
+        lo = __builtin_amdgcn_update_dpp(0, lo, 0x130, 0xf, 0xf, false);  // wave_shl:1
+        hi = __builtin_amdgcn_update_dpp(0, hi, 0x130, 0xf, 0xf, false);
     }
-    const double wgt = exp(-s * inv_s2);
-    raw[(b * M + m) * 256 + threadIdx.x] = wgt;
-    const int64_t qb = (int64_t)(qy / kWinTY) * tiles_x + qx / kWinTX;
-    const int ql = (qy % kWinTY) * kWinTX + qx % kWinTX;
-    raw[(qb * M + (M - 1 - m)) * 256 + ql] = wgt;
+    return __builtin_bit_cast(double, ((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo);
 }
 
-// d_p = sum over the window of w_pq in double, in increasing offset order
-// (increasing neighbour index), into the pixel-ordered degree array.
-__global__ __launch_bounds__(256) void window_degree_kernel(const double* __restrict__ raw, int32_t h, int32_t w,
-                                                            int32_t tiles_x, int32_t M, double* __restrict__ d,
-                                                            int32_t* flags, unsigned long long* first_bad) {
-    const int64_t b = blockIdx.x;
-    const int ty = (int)(b / tiles_x), tx = (int)(b - (int64_t)ty * tiles_x);
-    const int x = tx * kWinTX + (threadIdx.x & 63), y = ty * kWinTY + (threadIdx.x >> 6);
-    if (x >= w || y >= h) return;
+// A wavefront's patch distances: lane l holds column X0 + l of the padded image
+// J and rows Y0 .. Y0 + ROWS + 2 RP - 1, so that lanes RP .. 63 - RP form the
+// weights of the pixels x = X0 + l - RP, y = Y0 .. Y0 + ROWS - 1 to their
+// neighbours at one window offset.  The patch sum is separable: the squared
+// colour differences of the lane's column are combined down the rows, then
+// across the lanes with wave shifts, so a pair costs about (1 + 2 RP / ROWS)
+// colour differences instead of (2 RP + 1)^2.  Everything is double; the sums'
+// order is symmetric in the pair, so both of its ends form the same bits.
+template <int RP, int ROWS> struct WinPatch {
+    static constexpr int JR = ROWS + 2 * RP, OUT = 64 - 2 * RP;  // padded rows; pixels per row
+    float4 p[JR];
+
+    __device__ __forceinline__ void load(const float4* __restrict__ J, int64_t Jw, int64_t Jh, int X0, int Y0, int lane) {
+        const int64_t jc = min((int64_t)X0 + lane, Jw - 1);
+#pragma unroll
+        for (int a = 0; a < JR; ++a) p[a] = J[min((int64_t)Y0 + a, Jh - 1) * Jw + jc];
+    }
+
+    // sum over the patch for the offset (dy, dx) of every row
+    __device__ __forceinline__ void distance(const float4* __restrict__ J, int64_t Jw, int64_t Jh, int X0, int Y0,
+                                             int lane, int dy, int dx, bool c4, const WinAlpha& al,
+                                             double (&out)[ROWS]) const {
+        const int64_t jc = min(max((int64_t)X0 + lane + dx, (int64_t)0), Jw - 1);
+        double d[JR];
+#pragma unroll
+        for (int a = 0; a < JR; ++a) {
+            const int64_t jr = min(max((int64_t)Y0 + a + dy, (int64_t)0), Jh - 1);
+            const float4 q = J[jr * Jw + jc];
+            const double d0 = (double)p[a].x - (double)q.x, d1 = (double)p[a].y - (double)q.y;
+            const double d2 = (double)p[a].z - (double)q.z;
+            d[a] = (d0 * d0 + d1 * d1) + d2 * d2;
+            if (c4) {
+                const double d3 = (double)p[a].w - (double)q.w;
+                d[a] += d3 * d3;
+            }
+        }
+#pragma unroll
+        for (int y = 0; y < ROWS; ++y) {
+            double v = al.g[0] * d[y + RP];
+#pragma unroll
+            for (int k = 1; k <= RP; ++k) v += al.g[k] * (d[y + RP - k] + d[y + RP + k]);
+            double s = al.g[0] * v, lo = v, hi = v;
+#pragma unroll
+            for (int k = 1; k <= RP; ++k) {
+                lo = lane_shift(lo, true);
+                hi = lane_shift(hi, false);
+                s += al.g[k] * (lo + hi);
+            }
+            out[y] = s;
+        }
+    }
+};
+
+constexpr int kDegRows = 8;   // image rows of a degree workgroup
+constexpr int kDegWaves = 8;  // its wavefronts, each taking every eighth window row
+
+// d_p = sum over the window of w_pq in double, and its root: wavefront v of a
+// workgroup sums the window rows v, v + 8, .. of its pixels, offsets in order,
+// and the eight sums are added in order.  The weights are formed here and again
+// by window_fill_kernel rather than kept: their F64 copy was 8 bytes per pixel
+// and offset (5.2 GB for a 1024 x 1024 image with the 25 x 25 window), written
+// once and read twice, and allocating it cost more than forming them.
+template <int RP>
+__global__ __launch_bounds__(64 * kDegWaves) void window_degree_kernel(const float4* __restrict__ J, int32_t h, int32_t w,
+                                                                       int32_t r, bool c4, WinAlpha al, double inv_s2,
+                                                                       double* __restrict__ d, double* __restrict__ root,
+                                                                       int32_t* flags, unsigned long long* first_bad) {
+    typedef WinPatch<RP, kDegRows> P;
+    __shared__ double part[kDegWaves][kDegRows][64];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int strips = (w + P::OUT - 1) / P::OUT, by = (int)(blockIdx.x / strips);
+    const int X0 = ((int)blockIdx.x - by * strips) * P::OUT, Y0 = by * kDegRows;
+    const int64_t Jw = (int64_t)w + 2 * RP, Jh = (int64_t)h + 2 * RP;
+    const int x = X0 + lane - RP;
+    const bool col = lane >= RP && lane < 64 - RP && x < w;
+    P pt;
+    pt.load(J, Jw, Jh, X0, Y0, lane);
+    double acc[kDegRows];
+#pragma unroll
+    for (int y = 0; y < kDegRows; ++y) acc[y] = 0.0;
+    for (int dy = wave - r; dy <= r; dy += kDegWaves) {
+        if (Y0 + kDegRows - 1 + dy < 0 || Y0 + dy >= h) continue;  // no row of the workgroup has such a neighbour
+        for (int dx = -r; dx <= r; ++dx) {
+            if (dy == 0 && dx == 0) continue;
+            double s[kDegRows];
+            pt.distance(J, Jw, Jh, X0, Y0, lane, dy, dx, c4, al, s);
+            const bool in = col && x + dx >= 0 && x + dx < w;
+#pragma unroll
+            for (int y = 0; y < kDegRows; ++y) {
+                const int qy = Y0 + y + dy;
+                const double wgt = exp(-s[y] * inv_s2);
+                if (in && qy >= 0 && qy < h) acc[y] += wgt;
+            }
+        }
+    }
+#pragma unroll
+    for (int y = 0; y < kDegRows; ++y) part[wave][y][lane] = acc[y];
+    __syncthreads();
+    // wavefront v finishes row v
+    const int y = Y0 + wave;
+    if (!col || y >= h) return;
     double s = 0.0;
-    for (int m = 0; m < M; ++m) s += raw[(b * M + m) * 256 + threadIdx.x];
+#pragma unroll
+    for (int v = 0; v < kDegWaves; ++v) s += part[v][wave][lane];
     const int64_t p = (int64_t)y * w + x;
     d[p] = s;
+    root[p] = sqrt(s);
     if (!(s > 0.0) || !(s <= 1.7976931348623157e308)) {
         atomicOr(flags, (int32_t)BAD_DEGREE);
         atomicMin(first_bad, (unsigned long long)p);
     }
 }
 
-// Stored weights: what_pq = w_pq / sqrt(d_p d_q) (raw = 0) or w_pq (raw != 0),
-// rounded once to TW, for the first half of each pixel's window; one block per
-// (tile, vector of GS offsets).
-template <typename TW>
-__global__ __launch_bounds__(256) void window_fill_kernel(const double* __restrict__ raw,
-                                                          const double* __restrict__ d, int32_t h, int32_t w,
-                                                          int32_t r, int32_t tiles_x, int32_t M, int32_t raw_mode,
+// Stored weights: what_pq = w_pq / (sqrt(d_p) sqrt(d_q)) (raw = 0) or w_pq (raw !=
+// 0), rounded once to TW, for the first half of each pixel's window: a
+// wavefront per 4 image rows x OUT columns and vector of GS offsets.  Ragged
+// tiles' lanes outside the image, offsets outside it and padding store 0.
+template <int RP, typename TW>
+__global__ __launch_bounds__(256) void window_fill_kernel(const float4* __restrict__ J, const double* __restrict__ root,
+                                                          int32_t h, int32_t w, int32_t r, int32_t tiles_x, int32_t M,
+                                                          bool c4, WinAlpha al, double inv_s2, int32_t raw_mode,
                                                           u32x4* __restrict__ out) {
+    typedef WinPatch<RP, kWinTY> P;
     constexpr int GS = 16 / (int)sizeof(TW);
-    const int64_t b = blockIdx.x;
-    const int g = blockIdx.y, ng = window_groups(M, GS);
-    const int side = 2 * r + 1;
-    const int ty = (int)(b / tiles_x), tx = (int)(b - (int64_t)ty * tiles_x);
-    const int x = tx * kWinTX + (threadIdx.x & 63), y = ty * kWinTY + (threadIdx.x >> 6);
-    const bool ok = x < w && y < h;
-    const double dp = ok ? d[(int64_t)y * w + x] : 1.0;
-    TW vals[GS];
+    const int ng = window_groups(M, GS), side = 2 * r + 1;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int g = (int)blockIdx.y * 4 + wave;
+    if (g >= ng) return;
+    const int strips = (tiles_x * kWinTX + P::OUT - 1) / P::OUT;
+    const int ty = (int)(blockIdx.x / strips), X0 = ((int)blockIdx.x - ty * strips) * P::OUT, Y0 = ty * kWinTY;
+    const int64_t Jw = (int64_t)w + 2 * RP, Jh = (int64_t)h + 2 * RP;
+    const int x = X0 + lane - RP;
+    const bool col = x < w;
+    P pt;
+    pt.load(J, Jw, Jh, X0, Y0, lane);
+    double rp_[kWinTY];
 #pragma unroll
+    for (int y = 0; y < kWinTY; ++y)
+        rp_[y] = col && x >= 0 && Y0 + y < h ? root[(int64_t)(Y0 + y) * w + x] : 1.0;
+    // the vector of a pixel is shifted in from the top, one weight at a time
+    u32x4 v[kWinTY];
+#pragma unroll
+    for (int y = 0; y < kWinTY; ++y) v[y] = u32x4{0u, 0u, 0u, 0u};
     for (int e = 0; e < GS; ++e) {
         const int m = g * GS + e;
-        double o = 0.0;
-        if (m < M / 2) {
-            const double wv = raw[(b * M + m) * 256 + threadIdx.x];
-            if (ok && wv != 0.0) {
-                const int dy = m / side - r, dx = m - (m / side) * side - r;  // the cell index of the scan equals m
-                const double dq = d[(int64_t)(y + dy) * w + (x + dx)];
-                o = raw_mode ? wv : wv / (sqrt(dp) * sqrt(dq));
+        const int dy = m / side - r, dx = m - (m / side) * side - r;  // the cell index of the scan equals m
+        double s[kWinTY];
+        const bool live = m < M / 2;
+        if (live) pt.distance(J, Jw, Jh, X0, Y0, lane, dy, dx, c4, al, s);
+        const bool in = live && col && x >= 0 && x + dx >= 0 && x + dx < w;
+#pragma unroll
+        for (int y = 0; y < kWinTY; ++y) {
+            const int qy = Y0 + y + dy;
+            double o = 0.0;
+            if (in && Y0 + y < h && qy >= 0) {
+                o = exp(-s[y] * inv_s2);
+                if (!raw_mode && o != 0.0) o = o / (rp_[y] * root[(int64_t)qy * w + x + dx]);
+            }
+            const TW q = store_as<TW>::from(o);
+            if constexpr (sizeof(TW) == 8) {
+                uint64_t b;
+                __builtin_memcpy(&b, &q, 8);
+                v[y] = u32x4{v[y].z, v[y].w, (uint32_t)b, (uint32_t)(b >> 32)};
+            } else if constexpr (sizeof(TW) == 4) {
+                uint32_t b;
+                __builtin_memcpy(&b, &q, 4);
+                v[y] = u32x4{v[y].y, v[y].z, v[y].w, b};
+            } else {
+                uint16_t b;
+                __builtin_memcpy(&b, &q, 2);
+                v[y] = u32x4{(v[y].x >> 16) | (v[y].y << 16), (v[y].y >> 16) | (v[y].z << 16),
+                             (v[y].z >> 16) | (v[y].w << 16), (v[y].w >> 16) | ((uint32_t)b << 16)};
             }
         }
-        vals[e] = store_as<TW>::from(o);
     }
-    u32x4 v;
-    __builtin_memcpy(&v, vals, 16);
-    out[(b * ng + g) * 256 + threadIdx.x] = v;
+    if (lane < RP || lane >= 64 - RP || x >= tiles_x * kWinTX) return;
+    const int64_t tile = (int64_t)ty * tiles_x + x / kWinTX;
+#pragma unroll
+    for (int y = 0; y < kWinTY; ++y) out[(tile * ng + g) * 256 + y * kWinTX + x % kWinTX] = v[y];
 }
 
 // Unnormalized L: diagonal dd_p = sum of the stored weights of p's whole window
@@ -159,13 +262,45 @@ __global__ __launch_bounds__(256) void window_rowsum_kernel(const TW* __restrict
     dd[(int64_t)y * w + x] = (A)s;
 }
 
-template <typename TW>
-hipError_t launch_fill_t(const double* raw, const double* d, const gl_operator* op, int raw_mode, hipStream_t s) {
-    const int GS = 16 / (int)sizeof(TW);
-    const dim3 grid((unsigned)op->nblocks, (unsigned)window_groups(op->wM, GS));
-    hipLaunchKernelGGL(window_fill_kernel<TW>, grid, dim3(256), 0, s, raw, d, op->wheight, op->wwidth, op->wr,
-                       op->wtiles_x, op->wM, raw_mode, (u32x4*)op->w);
+// Patch radius and colours, and what the two passes over the weights need.
+struct WinBuild {
+    const float4* J;
+    const double* root;
+    int32_t rp;
+    bool c4;
+    WinAlpha al;
+    double inv_s2;
+};
+
+template <int RP>
+hipError_t launch_degree_t(const WinBuild& b, const gl_operator* op, double* root, int32_t* flags,
+                           unsigned long long* first_bad, hipStream_t s) {
+    constexpr int out = WinPatch<RP, kDegRows>::OUT;
+    const dim3 grid((unsigned)((op->wwidth + out - 1) / out * ((op->wheight + kDegRows - 1) / kDegRows)));
+    hipLaunchKernelGGL(window_degree_kernel<RP>, grid, dim3(64 * kDegWaves), 0, s, b.J, op->wheight, op->wwidth, op->wr,
+                       b.c4, b.al, b.inv_s2, op->degree, root, flags, first_bad);
     return hipGetLastError();
+}
+
+template <int RP, typename TW>
+hipError_t launch_fill_t(const WinBuild& b, const gl_operator* op, int raw_mode, hipStream_t s) {
+    constexpr int GS = 16 / (int)sizeof(TW), out = WinPatch<RP, kWinTY>::OUT;
+    const int tiles_y = (op->wheight + kWinTY - 1) / kWinTY;
+    const int strips = (op->wtiles_x * kWinTX + out - 1) / out;
+    const dim3 grid((unsigned)(strips * tiles_y), (unsigned)((window_groups(op->wM, GS) + 3) / 4));
+    hipLaunchKernelGGL((window_fill_kernel<RP, TW>), grid, dim3(256), 0, s, b.J, b.root, op->wheight, op->wwidth, op->wr,
+                       op->wtiles_x, op->wM, b.c4, b.al, b.inv_s2, raw_mode, (u32x4*)op->w);
+    return hipGetLastError();
+}
+
+template <int RP>
+hipError_t launch_fill(const WinBuild& b, const gl_operator* op, int raw_mode, hipStream_t s) {
+    switch (op->store_w) {
+        case GL_F64: return launch_fill_t<RP, double>(b, op, raw_mode, s);
+        case GL_F32: return launch_fill_t<RP, float>(b, op, raw_mode, s);
+        case GL_BF16: return launch_fill_t<RP, bf16>(b, op, raw_mode, s);
+        default: return launch_fill_t<RP, f16>(b, op, raw_mode, s);
+    }
 }
 
 template <typename TW, typename A>
@@ -267,7 +402,6 @@ extern "C" gl_status gl_window_operator_create(const gl_window_graph* g, gl_dtyp
     const int64_t n = (int64_t)h * w;
     const int GS = 16 / (int)wdtype_size(store_w);
     const int64_t stored = ntiles * 256 * window_groups(M, GS) * GS;  // first half of each window, padded
-    const int64_t rawn = ntiles * 256 * M;                             // F64 weights of the whole windows
 
     gl_operator* op = new gl_operator();
     op->n = n;
@@ -290,33 +424,33 @@ extern "C" gl_status gl_window_operator_create(const gl_window_graph* g, gl_dtyp
     (void)hipGetDevice(&op->device);
 
     // patch weights: separable Gaussian normalised to sum 1
-    WinAlpha al = {};
+    WinBuild build = {};
+    build.rp = rp;
+    build.c4 = g->channels == 4;
+    build.inv_s2 = 1.0 / (g->sigma * g->sigma);
     {
-        const int pw = 2 * rp + 1;
-        std::vector<double> gg(pw);
         double gs = 0.0;
-        for (int t = -rp; t <= rp; ++t) {
-            gg[t + rp] = rp > 0 ? std::exp(-(double)t * t / (2.0 * rp * rp)) : 1.0;
-            gs += gg[t + rp];
+        for (int t = 0; t <= rp; ++t) {
+            build.al.g[t] = rp > 0 ? std::exp(-(double)t * t / (2.0 * rp * rp)) : 1.0;
+            gs += (t ? 2.0 : 1.0) * build.al.g[t];
         }
-        for (int a = 0; a < pw; ++a)
-            for (int c = 0; c < pw; ++c) al.a[a * pw + c] = gg[a] * gg[c] / (gs * gs);
+        for (int t = 0; t <= rp; ++t) build.al.g[t] /= gs;
     }
 
     const size_t wbytes = (size_t)stored * wdtype_size(store_w);
     const size_t Jn = (size_t)(h + 2 * rp) * (size_t)(w + 2 * rp);
     float4* J = nullptr;
-    double* raw = nullptr;
+    double* root = nullptr;  // sqrt of the degrees
     int32_t* flags = nullptr;
     std::string what;
     hipError_t e = hipMalloc(&op->w, wbytes);
     if (e == hipSuccess) e = hipMalloc((void**)&op->degree, (size_t)n * 8);
     if (e == hipSuccess) e = hipMalloc((void**)&J, Jn * sizeof(float4));
-    if (e == hipSuccess) e = hipMalloc((void**)&raw, (size_t)rawn * 8);
+    if (e == hipSuccess) e = hipMalloc((void**)&root, (size_t)n * 8);
     if (e == hipSuccess) e = hipMalloc((void**)&flags, 16);
     if (e != hipSuccess) {
         (void)hipFree(J);
-        (void)hipFree(raw);
+        (void)hipFree(root);
         (void)hipFree(flags);
         gl_operator_destroy(op);
         (void)hipGetLastError();
@@ -329,21 +463,21 @@ extern "C" gl_status gl_window_operator_create(const gl_window_graph* g, gl_dtyp
     __builtin_memcpy(&hflags[2], &none, 8);
 
     e = hipMemcpyAsync(flags, hflags, 16, hipMemcpyHostToDevice, s);
-    if (e == hipSuccess) e = hipMemsetAsync(raw, 0, (size_t)rawn * 8, s);
     if (e == hipSuccess) {
         hipLaunchKernelGGL(window_pad_kernel, dim3((unsigned)((Jn + 255) / 256)), dim3(256), 0, s, g->image, h, w,
                            g->channels, rp, J);
         e = hipGetLastError();
     }
+    build.J = J;
+    build.root = root;
     if (e == hipSuccess) {
-        hipLaunchKernelGGL(window_raw_kernel, dim3((unsigned)ntiles, (unsigned)(M / 2)), dim3(256), 0, s,
-                           (const float4*)J, h, w, r, rp, tiles_x, M, al, 1.0 / (g->sigma * g->sigma), raw);
-        e = hipGetLastError();
-    }
-    if (e == hipSuccess) {
-        hipLaunchKernelGGL(window_degree_kernel, dim3((unsigned)ntiles), dim3(256), 0, s, (const double*)raw, h, w,
-                           tiles_x, M, op->degree, flags, first_bad);
-        e = hipGetLastError();
+        switch (rp) {
+            case 0: e = launch_degree_t<0>(build, op, root, flags, first_bad, s); break;
+            case 1: e = launch_degree_t<1>(build, op, root, flags, first_bad, s); break;
+            case 2: e = launch_degree_t<2>(build, op, root, flags, first_bad, s); break;
+            case 3: e = launch_degree_t<3>(build, op, root, flags, first_bad, s); break;
+            default: e = launch_degree_t<4>(build, op, root, flags, first_bad, s); break;
+        }
     }
     if (e == hipSuccess) e = hipMemcpyAsync(hflags, flags, 16, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
@@ -359,11 +493,12 @@ extern "C" gl_status gl_window_operator_create(const gl_window_graph* g, gl_dtyp
     }
     if (st == GL_OK) {
         const int raw_mode = op->lap == GL_LAP_UNNORMALIZED ? 1 : 0;
-        switch (store_w) {
-            case GL_F64: e = launch_fill_t<double>(raw, op->degree, op, raw_mode, s); break;
-            case GL_F32: e = launch_fill_t<float>(raw, op->degree, op, raw_mode, s); break;
-            case GL_BF16: e = launch_fill_t<bf16>(raw, op->degree, op, raw_mode, s); break;
-            default: e = launch_fill_t<f16>(raw, op->degree, op, raw_mode, s); break;
+        switch (rp) {
+            case 0: e = launch_fill<0>(build, op, raw_mode, s); break;
+            case 1: e = launch_fill<1>(build, op, raw_mode, s); break;
+            case 2: e = launch_fill<2>(build, op, raw_mode, s); break;
+            case 3: e = launch_fill<3>(build, op, raw_mode, s); break;
+            default: e = launch_fill<4>(build, op, raw_mode, s); break;
         }
         if (e == hipSuccess && raw_mode) {
             const size_t es = store_w == GL_F64 ? 8 : 4;
@@ -377,21 +512,11 @@ extern "C" gl_status gl_window_operator_create(const gl_window_graph* g, gl_dtyp
                     default: e = launch_rowsum_t<f16, float>(op, s); break;
                 }
             }
-            std::vector<char> hd;
-            if (e == hipSuccess) {
-                hd.resize((size_t)n * es);
-                e = hipMemcpyAsync(hd.data(), op->dd, hd.size(), hipMemcpyDeviceToHost, s);
-            }
-            if (e == hipSuccess) e = hipStreamSynchronize(s);
             double mx = 0.0;
-            for (int64_t i = 0; e == hipSuccess && i < n; ++i) {
-                const double v = es == 8 ? ((const double*)hd.data())[i] : (double)((const float*)hd.data())[i];
-                if (!(v > 0.0) || !std::isfinite(v)) {
-                    st = wfail(GL_E_BAD_GRAPH, "window graph: a stored row sums to a non-positive degree");
-                    break;
-                }
-                mx = v > mx ? v : mx;
-            }
+            bool bad = false;
+            if (e == hipSuccess) e = check_diagonal(op->dd, es == 8, n, flags, s, mx, bad);
+            if (e == hipSuccess && bad)
+                st = wfail(GL_E_BAD_GRAPH, "window graph: a stored row sums to a non-positive degree");
             op->dmax = mx;
         }
         if (e == hipSuccess) e = hipStreamSynchronize(s);
@@ -399,7 +524,7 @@ extern "C" gl_status gl_window_operator_create(const gl_window_graph* g, gl_dtyp
     }
     (void)hipStreamSynchronize(s);
     (void)hipFree(J);
-    (void)hipFree(raw);
+    (void)hipFree(root);
     (void)hipFree(flags);
     if (st != GL_OK) {
         gl_operator_destroy(op);

@@ -421,3 +421,30 @@ def test_full_size_sampled_rows(store_w, tol):
         worst = max(worst, abs(Y[i] - ref))
     say(f"  worst sampled-row error {worst:.3e}")
     assert worst <= tol
+
+
+# Edges of the construction: strips of 64 - 2 rp columns, 8-row degree blocks and
+# 4-row tiles, every patch radius and channel count.  F64 storage; the weights
+# differ from the oracle's by the order of a patch sum of at most 81 x 4 terms
+# (relative 1e-14 of an exponent below 60) and the degrees by that of the window.
+@pytest.mark.parametrize("h,w,rw,rp,ch", [(8, 64, 2, 0, 1), (9, 65, 3, 0, 4), (7, 62, 4, 1, 2), (16, 63, 3, 1, 3),
+                                         (9, 60, 5, 2, 4), (17, 121, 3, 2, 3), (4, 58, 4, 3, 1), (5, 117, 2, 3, 3),
+                                         (12, 56, 3, 4, 2), (3, 113, 6, 4, 4), (1, 130, 9, 2, 3), (33, 2, 7, 1, 3)])
+@pytest.mark.parametrize("laplacian", ["normalized", "unnormalized"])
+def test_construction_edges(h, w, rw, rp, ch, laplacian):
+    rng = np.random.default_rng(h * 1000 + w + rp)
+    img = (255.0 * rng.uniform(0, 1, (1, 1, ch)) + rng.normal(0, 3.0, (h, w, ch))).astype(np.float32)
+    n, sigma = h * w, 9.0
+    rp_, col, ww = wo.window_graph(img.astype(np.float64), rw, rp, sigma)
+    op = gl.Operator.window(torch.from_numpy(img).to(DEV), rw, rp, sigma, store_w="f64", laplacian=laplacian)
+    X = torch.from_numpy(rng.uniform(-1, 1, (n, 2))).to(DEV)
+    Y = op.laplacian_apply(X).cpu().numpy()
+    x = X.cpu().numpy()
+    row = np.repeat(np.arange(n), np.diff(rp_))
+    deg = np.bincount(row, ww, n)
+    lw = ww / np.sqrt(deg[row] * deg[col]) if laplacian == "normalized" else ww
+    ref = (np.ones(n) if laplacian == "normalized" else deg)[:, None] * x
+    np.subtract.at(ref, row, lw[:, None] * x[col])
+    err = np.abs(Y - ref).max()
+    say(f"window build {h}x{w} r={rw} rp={rp} channels={ch} {laplacian}: max err {err:.2e}")
+    assert err <= 1e-12 * max(1.0, deg.max() if laplacian == "unnormalized" else 1.0)
