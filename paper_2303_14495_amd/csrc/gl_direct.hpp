@@ -268,8 +268,8 @@ __global__ __launch_bounds__(kBlock) void laplacian_kernel(LapArgs<TW, TU, OffT>
 }
 
 // Power-method pass on float vectors with lx = L_s x = x - What x (or L x =
-// d x - W x).  mode 0: y = s lx with s = *scale, partial[0] = sum y^2.
-// mode 1: partial[0] = sum x lx, partial[1] = sum x^2.
+// d x - W x).  mode 0: y = s lx with s = gain *scale (gain when scale is NULL),
+// partial[0] = sum y^2.  mode 1: partial[0] = sum x lx, partial[1] = sum x^2.  mode 2: y = s lx.
 template <typename TW, typename OffT> struct PowerArgs {
     const OffT* rp;
     const int32_t* col;
@@ -282,6 +282,7 @@ template <typename TW, typename OffT> struct PowerArgs {
     const float* dd;  // d_i of L, or nullptr for L_s
     RowGeom g;
     int32_t mode;
+    float gain;
 };
 
 template <typename TW, typename OffT>
@@ -292,7 +293,7 @@ __global__ __launch_bounds__(kBlock) void power_kernel(PowerArgs<TW, OffT> a) {
     const int rows_per_tile = kBlock >> a.g.log2G;
     const int64_t b = a.g.remap ? xcd_remap(blockIdx.x, gridDim.x) : (int64_t)blockIdx.x;
     const int64_t row0 = b * a.g.rows_per_block;
-    const float s = a.mode == 0 ? *a.scale : 1.0f;
+    const float s = a.scale ? a.gain * *a.scale : a.gain;
     float p0 = 0.f, p1 = 0.f;
     for (int t = 0; t < a.g.tiles; ++t) {
         const int64_t row = row0 + (int64_t)t * rows_per_tile + grp;
@@ -302,7 +303,7 @@ __global__ __launch_bounds__(kBlock) void power_kernel(PowerArgs<TW, OffT> a) {
             const int64_t node = a.order ? (int64_t)a.order[row] : row;
             const float xv = a.x[node];
             const float lx = (a.dd ? a.dd[node] * xv : xv) - z[0];
-            if (a.mode == 0) {
+            if (a.mode != 1) {
                 const float yv = s * lx;
                 a.y[node] = yv;
                 p0 += yv * yv;
@@ -313,7 +314,7 @@ __global__ __launch_bounds__(kBlock) void power_kernel(PowerArgs<TW, OffT> a) {
         }
     }
     float e[1] = {p0}, r[1] = {p1};
-    block_stats<1, 1>(e, r, G, a.partials, (int64_t)gridDim.x, b);
+    if (a.mode != 2) block_stats<1, 1>(e, r, G, a.partials, (int64_t)gridDim.x, b);
 }
 
 }  // namespace gl

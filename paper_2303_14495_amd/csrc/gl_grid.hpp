@@ -411,6 +411,7 @@ struct GridPowerArgs {
     float* partials;
     const float* dd;
     int32_t mode;
+    float gain;
 };
 
 template <typename TW>
@@ -418,7 +419,7 @@ __global__ __launch_bounds__(kGridThreads) void grid_power_kernel(GridPowerArgs 
     extern __shared__ unsigned char smem_raw[];
     void* hv = smem_raw;
     const int64_t b = xcd_remap(blockIdx.x, gridDim.x);
-    const float s = a.mode == 0 ? *a.scale : 1.0f;
+    const float s = a.scale ? a.gain * *a.scale : a.gain;
     float dl = 1.f, p0 = 0.f, p1 = 0.f;
     auto prefetch = [&](bool ok, int64_t p) {
         if (ok && a.dd) dl = a.dd[p];
@@ -427,7 +428,7 @@ __global__ __launch_bounds__(kGridThreads) void grid_power_kernel(GridPowerArgs 
         if (!ok) return;
         const float xv = vc[0];
         const float lx = (a.dd ? dl * xv : xv) - z[0];
-        if (a.mode == 0) {
+        if (a.mode != 1) {
             const float yv = s * lx;
             a.y[p] = yv;
             p0 += yv * yv;
@@ -438,7 +439,7 @@ __global__ __launch_bounds__(kGridThreads) void grid_power_kernel(GridPowerArgs 
     };
     grid_products<1, TW, float, float>(a.op, a.x, b, hv, prefetch, finish);
     float e[1] = {p0}, r[1] = {p1};
-    block_stats_lanes<1, kGridTY>(e, r, a.partials, (int64_t)gridDim.x, b);
+    if (a.mode != 2) block_stats_lanes<1, kGridTY>(e, r, a.partials, (int64_t)gridDim.x, b);
 }
 
 // Unnormalized L on the grid layout: dd_i = sum over row i of the weights as

@@ -126,7 +126,7 @@ hipError_t check_diagonal(const void* dd, bool f64, int64_t n, void* scratch, hi
 
 // Power-method pass on the window layout (see gl::window_power_kernel); part:
 // window_part_bytes(op, 1, 4) bytes.
-hipError_t launch_window_power(const gl_operator* op, const float* x, float* y, int mode, const float* scale,
+hipError_t launch_window_power(const gl_operator* op, const float* x, float* y, int mode, float gain, const float* scale,
                                float* partials, float* part, hipStream_t s);
 
 // gl_knn for 64 < d <= 4096 (arguments checked by the caller); *fallback_rows

@@ -356,6 +356,7 @@ struct TilePowerArgs {
     float* partials;
     const float* dd;  // d_i of L by position, or nullptr for L_s
     int32_t mode;
+    float gain;
 };
 
 template <typename TW>
@@ -365,7 +366,7 @@ __global__ __launch_bounds__(256) void tile_power_kernel(TilePowerArgs a) {
     const int q = threadIdx.x & (kTileG - 1);
     TileRows rows;
     float xx[kTilePasses], dx[kTilePasses];
-    const float s = a.mode == 0 ? *a.scale : 1.0f;
+    const float s = a.scale ? a.gain * *a.scale : a.gain;
     float p0 = 0.f, p1 = 0.f;
     auto prefetch = [&](TileRows& r) {
 #pragma unroll
@@ -378,7 +379,7 @@ __global__ __launch_bounds__(256) void tile_power_kernel(TilePowerArgs a) {
         constexpr int tt = decltype(TT)::value;
         if (!rows.ok[tt] || q != 0) return;
         const float lx = dx[tt] - z[0];
-        if (a.mode == 0) {
+        if (a.mode != 1) {
             const float yv = s * lx;
             a.y[rows.node[tt]] = yv;
             p0 += yv * yv;
@@ -389,7 +390,7 @@ __global__ __launch_bounds__(256) void tile_power_kernel(TilePowerArgs a) {
     };
     tile_products<1, TW, float, float>(a.op, a.x, (int64_t)blockIdx.x, hv, rows, prefetch, finish);
     float e[1] = {p0}, r[1] = {p1};
-    block_stats<1, 1>(e, r, kTileG, a.partials, (int64_t)gridDim.x, (int64_t)blockIdx.x);
+    if (a.mode != 2) block_stats<1, 1>(e, r, kTileG, a.partials, (int64_t)gridDim.x, (int64_t)blockIdx.x);
 }
 
 // Fill the tile (or direct) weight array: entry e of position p takes the

@@ -347,7 +347,7 @@ static void window_power_t(const WinPowerArgs& a, const gl_operator* op, hipStre
     hipLaunchKernelGGL(window_power_kernel<TW>, grid, block, 0, s, a);
 }
 
-hipError_t launch_window_power(const gl_operator* op, const float* x, float* y, int mode, const float* scale,
+hipError_t launch_window_power(const gl_operator* op, const float* x, float* y, int mode, float gain, const float* scale,
                                float* partials, float* part, hipStream_t s) {
     WinPowerArgs a;
     a.op.w = op->w;
@@ -363,6 +363,7 @@ hipError_t launch_window_power(const gl_operator* op, const float* x, float* y, 
     a.partials = partials;
     a.dd = (const float*)op->dd;
     a.mode = mode;
+    a.gain = gain;
     switch (op->store_w) {
         case GL_F32: window_power_t<float>(a, op, s); break;
         case GL_BF16: window_power_t<bf16>(a, op, s); break;

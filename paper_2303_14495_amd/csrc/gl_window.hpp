@@ -343,12 +343,13 @@ struct WinPowerArgs {
     float* partials;
     const float* dd;
     int32_t mode;
+    float gain;
 };
 
 template <typename TW>
 __global__ __launch_bounds__(256) void window_power_kernel(WinPowerArgs a) {
     const WinPixel q = window_pixel(a.op);
-    const float s = a.mode == 0 ? *a.scale : 1.0f;
+    const float s = a.scale ? a.gain * *a.scale : a.gain;
     float p0 = 0.f, p1 = 0.f;
     if (q.ok) {
         const float dl = a.dd ? a.dd[q.p] : 1.f;
@@ -356,7 +357,7 @@ __global__ __launch_bounds__(256) void window_power_kernel(WinPowerArgs a) {
         float z[1];
         window_gather<1, float>(a.op, a.part, q.y, q.x, z);
         const float lx = (a.dd ? dl * xv : xv) - z[0];
-        if (a.mode == 0) {
+        if (a.mode != 1) {
             const float yv = s * lx;
             a.y[q.p] = yv;
             p0 += yv * yv;
@@ -366,7 +367,7 @@ __global__ __launch_bounds__(256) void window_power_kernel(WinPowerArgs a) {
         }
     }
     float e[1] = {p0}, r[1] = {p1};
-    block_stats<1, 1>(e, r, 1, a.partials, (int64_t)gridDim.x, q.b);
+    if (a.mode != 2) block_stats<1, 1>(e, r, 1, a.partials, (int64_t)gridDim.x, q.b);
 }
 
 }  // namespace gl
