@@ -290,8 +290,8 @@ gl_status gl_power_max_eig(const gl_operator *op, int32_t iters, const float *x0
  *             row, no self-loops): a gl_graph ready for gl_operator_create
  *   capacity  >= 2 n k;  *nnz (host out)
  * 2 <= n < 2^31, 1 <= k <= min(n-1, 1024), 2 n k < 2^31, 1 <= scale_rank <= k.
- * Allocates about 48 n k bytes of stream-ordered temporaries; synchronises
- * `stream`.  Errors: GL_E_INVALID_ARG (also an index out of range or equal
+ * Allocates about 32 n k bytes of stream-ordered temporaries (80 n k when k > 24 or
+ * a point is in more than 4096 lists); synchronises `stream`.  Errors: GL_E_INVALID_ARG (also an index out of range or equal
  * to its row, a negative or non-finite distance), GL_E_BAD_GRAPH (a point
  * whose weights are all 0), GL_E_NOMEM, GL_E_HIP. */
 gl_status gl_knn_graph(int64_t n, int32_t k, const int32_t *idx, const float *d2, int32_t scale_rank,

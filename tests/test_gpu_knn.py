@@ -255,6 +255,46 @@ def test_knn_graph_duplicates_and_errors():
             _graph_gpu(bad_i, bad_d, 1)
 
 
+def _lists_with_row(n, length):
+    """Lists of 2 whose union gives point 5 a row of `length` entries before
+    duplicates go: its own two and those of length - 2 points."""
+    idx = np.empty((n, 2), np.int32)
+    for i in range(n):
+        ring = [j for j in ((i + s) % n for s in range(1, 5)) if j != 5]
+        idx[i] = (5, ring[0]) if i != 5 and (i < length - 1) else (ring[0], ring[1])
+    assert int((idx == 5).sum()) == length - 2
+    return idx
+
+
+@pytest.mark.parametrize("case", [63, 64, 65, 4096, 4097, 12290, "dense", "repeated"])
+def test_knn_graph_row_lengths(case):
+    """Rows at the edges of a wavefront (64 entries), of one sorted run (4096) and
+    of several; lists of 70 (every row long); a point repeated within a list.
+    Distances are a symmetric function of the pair and some weights vanish.
+    The weight is one float64 division and exponential on both sides: 4 ulp."""
+    rng = np.random.default_rng(7)
+    if case == "dense":
+        n = 300
+        idx = np.stack([rng.permutation(np.delete(np.arange(n), i))[:70] for i in range(n)]).astype(np.int32)
+    elif case == "repeated":
+        n = 40
+        idx = ((np.arange(n)[:, None] + rng.integers(1, 4, (n, 9))) % n).astype(np.int32)
+    else:
+        n = case + 30
+        idx = _lists_with_row(n, case)
+    i = np.arange(n)[:, None]
+    lo, hi = np.minimum(i, idx).astype(np.int64), np.maximum(i, idx).astype(np.int64)
+    d2 = (0.5 + (lo * 31 + hi * 17) % 97 / 64.0).astype(np.float32)
+    d2[((lo + hi) % 13 == 0) & (hi - lo > 4)] = 1e5
+    rank = idx.shape[1]
+    say(f"knn graph rows {case}")
+    rp, col, w = _graph_gpu(idx, d2, rank)
+    orp, ocol, ow = knn_oracle.graph_from_knn(n, idx, d2.astype(np.float64), rank)
+    assert rp.tolist() == orp.tolist()
+    assert col.tolist() == ocol.tolist()
+    assert np.all(np.abs(w - ow) <= 4 * np.spacing(ow))
+
+
 # ---------------------------------------------------------------------------
 # wide features (d > 64): f16 Gram matrix on the matrix cores, exact refine,
 # certificate, exact rescan of uncertified rows
