@@ -522,12 +522,13 @@ gl_status gl_server_destroy(gl_server *srv);
  * the matrix cores: <x_i, x_j> of the centred points rounded to f16 (scaled
  * by a power of two), f32 accumulation, in one fused kernel that filters
  * every block of products into per-query candidate lists without storing
- * them; per query 64 candidates get their exact distances recomputed, and a
- * certificate from the rounding-error bound proves that no other point can
+ * them; the candidates of a query that can be among the k best get their
+ * exact distances recomputed (64 at most), and a certificate from the rounding-error bound proves that no other point can
  * enter or tie the k best; queries without it are rescanned exactly
  * (gl_knn_fallback_rows).  Non-finite coordinates are rejected
- * (GL_E_INVALID_ARG).  Allocates about n (2 d + 300) bytes as
- * stream-ordered temporaries and synchronises `stream`.
+ * (GL_E_INVALID_ARG).  Allocates about n (2 d + 1100) bytes, below
+ * 16 384 points up to n (2 d + 6200), as stream-ordered temporaries and
+ * synchronises `stream`.
  * Errors: GL_E_INVALID_ARG, GL_E_NOMEM, GL_E_HIP. */
 gl_status gl_knn(const float *x, int64_t n, int32_t d, int32_t k, int32_t *idx_out,
                  float *d2_out, void *stream);

@@ -346,6 +346,38 @@ def test_knn_wide_block_edges(n, d, k):
     assert np.abs(d2 - ref).max() <= 1e-6 * max(1.0, float(ref.max()))
 
 
+@pytest.mark.parametrize("n,d,k", [(255, 96, 10), (257, 97, 32), (768, 65, 12), (769, 127, 13), (1025, 160, 32),
+                                   (16384, 65, 10), (16385, 96, 12), (17000, 70, 32)])
+def test_knn_wide_plan_edges(n, d, k):
+    """Points around the 256-point blocks and the 4 segments of a query block (every
+    fourth point each below 769), lists of 8 for k <= 12 and of 12 above, coordinates around
+    the 32 of a staging step, and query blocks around one full round of 64 (16384
+    points: none left over, then one and three cut into 16 segments)."""
+    x = mixture(n, d, seed=n + d + k)
+    say(f"wide knn plan n={n} d={d} k={k}")
+    idx, d2 = gl.knn(torch.from_numpy(x).to(DEV), k)
+    fb = gl.knn_fallback_rows()
+    idx, d2 = idx.cpu().numpy(), d2.cpu().numpy()
+    rows = np.unique(np.concatenate([np.arange(0, n, max(1, n // 400)), np.arange(max(0, n - 40), n)]))
+    check(x, k, idx[rows], d2[rows], rows)
+    say(f"  exact rescans {fb}")
+    assert fb <= n // 20
+    ref = _exact_f32(x, rows, idx[rows])
+    assert np.abs(d2[rows] - ref).max() <= 1e-6 * max(1.0, float(ref.max()))
+
+
+def test_knn_wide_many_copies():
+    """20 integer points, 100 copies of each: more points within the error bound of
+    the k-th distance than a wavefront refines, so the rescan decides the ties."""
+    rng = np.random.default_rng(3)
+    x = np.repeat(rng.integers(0, 9, (20, 80)), 100, axis=0).astype(np.float32)
+    x = x[rng.permutation(len(x))]
+    idx, d2 = gl.knn(torch.from_numpy(x).to(DEV), 12)
+    oi, od = knn_oracle.knn(x.astype(np.float64), 12)
+    assert np.array_equal(idx.cpu().numpy(), oi)
+    assert np.array_equal(d2.cpu().numpy(), od.astype(np.float32))
+
+
 def test_knn_wide_ties_use_the_exact_rescan():
     """The 96 unit vectors of R^96 are all at squared distance 2 from each
     other: every candidate ties with points outside the 64 candidates, so
