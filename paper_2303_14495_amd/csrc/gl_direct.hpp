@@ -91,9 +91,13 @@ __device__ __forceinline__ void update_column(const SweepArgs<TW, TU, OffT>& a, 
     if (a.vout) a.vout[node * K + k] = store_as<TU>::from(v + r * ginv);
     r_acc += r * r;
     if (a.energy) {
-        const A u2m1 = u * u - (A)1, dy = u - y;
+        // roundings written out, so that they are the same for every K
+        const A u2m1 = fma_acc(u, u, (A)-1), dy = u - y;
         const A ulu = fma_acc(u, a.dd ? dl * u : u, -(u * zk));  // u (L u)_i, one rounding
-        e_acc += a.k.half_eps * ulu + a.k.quarter_inv_eps * u2m1 * u2m1 + a.k.half_eta * lam * dy * dy;
+        A e = a.k.half_eps * ulu;
+        e = fma_acc(a.k.quarter_inv_eps * u2m1, u2m1, e);
+        e = fma_acc(a.k.half_eta * lam * dy, dy, e);
+        e_acc += e;
     }
 }
 
