@@ -428,14 +428,12 @@ __global__ __launch_bounds__(kGridThreads) void grid_power_kernel(GridPowerArgs 
         if (!ok) return;
         const float xv = vc[0];
         const float lx = (a.dd ? dl * xv : xv) - z[0];
-        if (a.mode != 1) {
-            const float yv = s * lx;
-            a.y[p] = yv;
-            p0 += yv * yv;
-        } else {
-            p0 += xv * lx;
-            p1 += xv * xv;
-        }
+        // one addition to each sum on every path: sums added to in branches were
+        // kept in scratch memory
+        const float yv = a.mode != 1 ? s * lx : lx;
+        if (a.mode != 1) a.y[p] = yv;
+        p0 += (a.mode != 1 ? yv : xv) * yv;
+        p1 += xv * xv;
     };
     grid_products<1, TW, float, float>(a.op, a.x, b, hv, prefetch, finish);
     float e[1] = {p0}, r[1] = {p1};

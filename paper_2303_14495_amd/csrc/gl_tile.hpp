@@ -379,14 +379,12 @@ __global__ __launch_bounds__(256) void tile_power_kernel(TilePowerArgs a) {
         constexpr int tt = decltype(TT)::value;
         if (!rows.ok[tt] || q != 0) return;
         const float lx = dx[tt] - z[0];
-        if (a.mode != 1) {
-            const float yv = s * lx;
-            a.y[rows.node[tt]] = yv;
-            p0 += yv * yv;
-        } else {
-            p0 += xx[tt] * lx;
-            p1 += xx[tt] * xx[tt];
-        }
+        // one addition to each sum on every path: sums added to in branches were
+        // kept in scratch memory
+        const float yv = a.mode != 1 ? s * lx : lx;
+        if (a.mode != 1) a.y[rows.node[tt]] = yv;
+        p0 += (a.mode != 1 ? yv : xx[tt]) * yv;
+        p1 += xx[tt] * xx[tt];
     };
     tile_products<1, TW, float, float>(a.op, a.x, (int64_t)blockIdx.x, hv, rows, prefetch, finish);
     float e[1] = {p0}, r[1] = {p1};
