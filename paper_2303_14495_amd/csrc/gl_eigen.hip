@@ -500,15 +500,19 @@ gl_status gl_second_eigenpair(const gl_operator* op, int32_t krylov, int32_t max
             return efail(GL_E_NONFINITE, "the start vector is zero or not finite");
         if (!(after > 1e-10 * before))
             return efail(GL_E_INVALID_ARG, "the start vector is parallel to the null vector");
-        // up to an invariant subspace: |w| at the rounding of float vectors (a graph
-        // with few distinct eigenvalues gets there); what is left of w then lies
-        // in the span of the vectors before it, and none after them is used
-        const double floor_ = 1e-6 * 2.0 * op->dmax;
+        // up to an invariant subspace: |w| at the rounding of L q_j itself (2^-24 of its
+        // entries; |L q_j|^2 = beta_{j-1}^2 + alpha_j^2 + beta_j^2).  Below it, the second
+        // Gram-Schmidt pass works on rounding errors and its result is no longer
+        // orthogonal to the vectors before it (a graph with few distinct eigenvalues
+        // gets there).  No multiple of dmax: a restart begins with beta_0 = the last
+        // residual, which L q_0 = lambda q_0 lets go far below 2^-24 dmax; one direction
+        // at that rounding does no harm yet, so the first step is cut at a quarter.
         a.clear();
         b.clear();
         for (int32_t j = 0; j < m; ++j) {
             a.push_back(host[j]);
-            if (j + 1 == m || !(host[m + j] > floor_)) break;
+            const double product = std::hypot(host[j], j > 0 ? host[m + j - 1] : 0.0);
+            if (j + 1 == m || !(host[m + j] > (j > 0 ? 4.0 : 1.0) * 0x1p-24 * product)) break;
             b.push_back(host[m + j]);
         }
         tridiag_smallest(a, b, theta, y);
@@ -527,7 +531,7 @@ gl_status gl_second_eigenpair(const gl_operator* op, int32_t krylov, int32_t max
         if (err == hipSuccess) err = hipStreamSynchronize(s);
         GE_CHECK("residual norm");
         res = std::sqrt(std::max(r2, 0.0));
-        if (res <= tol || restart >= max_restarts) break;
+        if (res <= tol || restart >= max_restarts || k == 1) break;  // k == 1: x is what it was
     }
     // sign: the entry of largest magnitude is positive
     float* sign = e.best + g256;
