@@ -268,7 +268,7 @@ gl_status check_params(const gl_params* p) {
 
 template <typename TIN, typename TOUT, typename OffT>
 void launch_normalize(gl_operator* op, const gl_graph* g, hipStream_t s) {
-    hipLaunchKernelGGL((gl::normalize_kernel<TIN, TOUT, OffT>), dim3(gl::row_grid(op->n + 1)), dim3(256), 0, s, op->n, g->row_ptr,
+    hipLaunchKernelGGL((gl::normalize_kernel<TIN, TOUT, OffT>), gl::row_grid(op->n + 1), dim3(256), 0, s, op->n, g->row_ptr,
                        g->col_idx, static_cast<const TIN*>(g->weight), op->degree, static_cast<OffT*>(op->rp),
                        op->col, static_cast<TOUT*>(op->w), op->lap == GL_LAP_UNNORMALIZED ? 1 : 0);
 }
@@ -568,11 +568,11 @@ gl_status gl_operator_create(const gl_graph* g, gl_dtype store_w, void* stream, 
     const unsigned grid = (unsigned)((g->n + 255) / 256);
     const int64_t heavy_min = gl::heavy_threshold(op->G);
     if (g->weight_dtype == GL_F64) {
-        hipLaunchKernelGGL(gl::validate_kernel<double>, dim3(gl::row_grid(g->n)), dim3(256), 0, s, g->n, g->nnz,
+        hipLaunchKernelGGL(gl::validate_kernel<double>, gl::row_grid(g->n), dim3(256), 0, s, g->n, g->nnz,
                            g->row_ptr, g->col_idx, (const double*)g->weight, heavy_min, op->degree,
                            (gl::GraphCheck*)scratch);
     } else {
-        hipLaunchKernelGGL(gl::validate_kernel<float>, dim3(gl::row_grid(g->n)), dim3(256), 0, s, g->n, g->nnz,
+        hipLaunchKernelGGL(gl::validate_kernel<float>, gl::row_grid(g->n), dim3(256), 0, s, g->n, g->nnz,
                            g->row_ptr, g->col_idx, (const float*)g->weight, heavy_min, op->degree,
                            (gl::GraphCheck*)scratch);
     }

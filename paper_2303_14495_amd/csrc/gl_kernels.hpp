@@ -2,6 +2,7 @@
 #pragma once
 
 #include "gl_device.hpp"
+#include "gl_fold.hpp"
 
 namespace gl {
 
@@ -268,7 +269,7 @@ __global__ __launch_bounds__(256) void validate_kernel(int64_t n, int64_t nnz, c
                                                        const int32_t* __restrict__ col, const TIN* __restrict__ w,
                                                        int64_t heavy_min, double* __restrict__ d,
                                                        GraphCheck* __restrict__ check) {
-    const int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kRowLanes;
+    const int64_t i = (folded(blockIdx.x, blockIdx.y, gridDim.x) * 256 + threadIdx.x) / kRowLanes;
     const int q = threadIdx.x % kRowLanes;
     if (i >= n) return;  // whole groups
     const int64_t beg = rp[i], end = rp[i + 1];
@@ -310,7 +311,7 @@ __global__ __launch_bounds__(256) void normalize_kernel(int64_t n, const int64_t
                                                         const double* __restrict__ d, OffT* __restrict__ rp_out,
                                                         int32_t* __restrict__ col_out, TOUT* __restrict__ w_out,
                                                         int32_t raw) {
-    const int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kRowLanes;
+    const int64_t i = (folded(blockIdx.x, blockIdx.y, gridDim.x) * 256 + threadIdx.x) / kRowLanes;
     const int q = threadIdx.x % kRowLanes;
     if (i > n) return;
     const int64_t beg = rp[i];
@@ -325,8 +326,12 @@ __global__ __launch_bounds__(256) void normalize_kernel(int64_t n, const int64_t
     }
 }
 
-// Workgroups of 256 threads for `rows` rows of kRowLanes lanes.
-inline unsigned row_grid(int64_t rows) { return (unsigned)((rows * kRowLanes + 255) / 256); }
+// Workgroups of 256 threads for `rows` rows of kRowLanes lanes (from 2^28 rows on, more
+// threads than one dimension of a launch holds).
+inline dim3 row_grid(int64_t rows) {
+    const Fold f = fold_blocks((rows * kRowLanes + 255) / 256);
+    return dim3(f.x, f.y);
+}
 
 // Diagonal of the unnormalized operator as stored: dd_p = sum of the row's
 // stored (rounded) weights, summed in double in storage order, rounded to A.

@@ -438,7 +438,7 @@ struct gl_server {
             s.u0.clear();
             s.u0.shrink_to_fit();
         };
-        hipLaunchKernelGGL(gl::validate_kernel<double>, dim3(gl::row_grid(s.n)), dim3(256), 0, st, s.n, s.nnz,
+        hipLaunchKernelGGL(gl::validate_kernel<double>, gl::row_grid(s.n), dim3(256), 0, st, s.n, s.nnz,
                            s.d_rp64, s.d_colin, s.d_win, gl::heavy_threshold(s.geom.G), s.d_deg,
                            (gl::GraphCheck*)s.d_flags);
         e = read_flags();
@@ -450,18 +450,18 @@ struct gl_server {
             drop_host_copies();
             return GL_E_BAD_GRAPH;
         }
-        const unsigned grid1 = gl::row_grid(s.n + 1);
+        const dim3 grid1 = gl::row_grid(s.n + 1);
         switch (cfg.store_w) {
             case GL_F32:
-                hipLaunchKernelGGL((gl::normalize_kernel<double, float, int32_t>), dim3(grid1), dim3(256), 0, st, s.n,
+                hipLaunchKernelGGL((gl::normalize_kernel<double, float, int32_t>), grid1, dim3(256), 0, st, s.n,
                                    s.d_rp64, s.d_colin, s.d_win, s.d_deg, s.d_rp, s.d_col, (float*)s.d_w, 0);
                 break;
             case GL_BF16:
-                hipLaunchKernelGGL((gl::normalize_kernel<double, gl::bf16, int32_t>), dim3(grid1), dim3(256), 0, st,
+                hipLaunchKernelGGL((gl::normalize_kernel<double, gl::bf16, int32_t>), grid1, dim3(256), 0, st,
                                    s.n, s.d_rp64, s.d_colin, s.d_win, s.d_deg, s.d_rp, s.d_col, (gl::bf16*)s.d_w, 0);
                 break;
             default:
-                hipLaunchKernelGGL((gl::normalize_kernel<double, gl::f16, int32_t>), dim3(grid1), dim3(256), 0, st,
+                hipLaunchKernelGGL((gl::normalize_kernel<double, gl::f16, int32_t>), grid1, dim3(256), 0, st,
                                    s.n, s.d_rp64, s.d_colin, s.d_win, s.d_deg, s.d_rp, s.d_col, (gl::f16*)s.d_w, 0);
                 break;
         }
