@@ -35,6 +35,7 @@
 
 #include "gl_internal.hpp"
 #include "gl_device.hpp"
+#include "gl_fold.hpp"
 
 namespace gl {
 namespace {
@@ -159,7 +160,7 @@ template <int KS>
 __global__ __launch_bounds__(256) void knn_pack_kernel(const float* __restrict__ x, int64_t n, int64_t np, int32_t d,
                                                        const KnnFrame* __restrict__ f, kn_h8* __restrict__ frag,
                                                        float* __restrict__ half_norm) {
-    const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const int64_t e = folded(blockIdx.x, blockIdx.y, gridDim.x) * 256 + threadIdx.x;
     if (e >= np * 2 * KS) return;
     const int64_t tile = e / (64 * KS);
     const int rest = (int)(e - tile * (64 * KS));
@@ -218,10 +219,11 @@ __global__ __launch_bounds__(64 * kTileWaves) void knn_tile_kernel(
     __shared__ float2 buf[kTileWaves][kBuf][64];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int half = lane >> 5, col = lane & 31;
-    const int qb = (int)blockIdx.x / segs;
-    const int seg = (int)blockIdx.x - qb * segs;
-    const int qt = qb * kTileWaves + wave;
-    if (qt >= tiles || f->bad) return;
+    const int64_t block = folded(blockIdx.x, blockIdx.y, gridDim.x);
+    const int qb = (int)(block / segs), seg = (int)(block - (int64_t)qb * segs);
+    const int64_t qt64 = (int64_t)qb * kTileWaves + wave;
+    if (qt64 >= tiles || f->bad) return;
+    const int qt = (int)qt64;
     const int64_t q = (int64_t)qt * 32 + col;
     const int t0 = (int)((int64_t)tiles * seg / segs), t1 = (int)((int64_t)tiles * (seg + 1) / segs);
 
@@ -363,7 +365,7 @@ __global__ __launch_bounds__(256) void knn_refine_kernel(const float* __restrict
     extern __shared__ float2 rsm[];  // [4][2 segs T] (distance, index)
     __shared__ float kth[4];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int64_t q = (int64_t)blockIdx.x * 4 + wave;
+    const int64_t q = folded(blockIdx.x, blockIdx.y, gridDim.x) * 4 + wave;
     const int C = 2 * segs * T;
     float2* sm = rsm + wave * C;
     const bool live = q < n, usable = live && !f->bad;
@@ -552,9 +554,12 @@ hipError_t knn_tile_launch(const float* x, int64_t n, int32_t d, int32_t T, int3
                            const KnnFrame* f, kn_h8* frag, float* half_norm, float* bound, int32_t* cand,
                            hipStream_t s) {
     const int64_t np = (int64_t)tiles * 32;
-    hipLaunchKernelGGL(knn_pack_kernel<KS>, dim3((unsigned)((np * 2 * KS + 255) / 256)), dim3(256), 0, s, x, n, np, d,
-                       f, frag, half_norm);
-    const dim3 grid((unsigned)((tiles + kTileWaves - 1) / kTileWaves * segs)), block(64 * kTileWaves);
+    // from 67 M points (the refinement) and 165 M (the operands of 64 coordinates) on, more
+    // threads than one dimension of a launch holds
+    const Fold fp = fold_blocks((np * 2 * KS + 255) / 256);
+    hipLaunchKernelGGL(knn_pack_kernel<KS>, dim3(fp.x, fp.y), dim3(256), 0, s, x, n, np, d, f, frag, half_norm);
+    const Fold ft = fold_blocks(((int64_t)tiles + kTileWaves - 1) / kTileWaves * segs);
+    const dim3 grid(ft.x, ft.y), block(64 * kTileWaves);
 #define GL_KNN_T(TT)                                                                                        \
     case TT:                                                                                                \
         hipLaunchKernelGGL((knn_tile_kernel<KS, TT>), grid, block, 0, s, x, n, d, f, (const kn_h8*)frag,    \
@@ -620,9 +625,10 @@ hipError_t knn_launch(const float* x, int64_t n, int32_t d, int32_t k, int32_t* 
         }
     }
     if (e == hipSuccess) {
-        hipLaunchKernelGGL(knn_refine_kernel, dim3((unsigned)((n + 3) / 4)), dim3(256), (size_t)4 * 2 * segs * T * 8,
-                           s, x, n, d, k, (const KnnFrame*)f, (const float*)half_norm, segs, T,
-                           (const float*)bound, (const int32_t*)cand, idx, d2, fails, fail_count);
+        const Fold fr = fold_blocks((n + 3) / 4);
+        hipLaunchKernelGGL(knn_refine_kernel, dim3(fr.x, fr.y), dim3(256), (size_t)4 * 2 * segs * T * 8, s, x, n, d, k,
+                           (const KnnFrame*)f, (const float*)half_norm, segs, T, (const float*)bound,
+                           (const int32_t*)cand, idx, d2, fails, fail_count);
         hipLaunchKernelGGL(knn_scan_kernel, dim3(1024), dim3(256), 0, s, x, n, d, k,
                            (const int32_t*)fails, (const unsigned int*)fail_count, idx, d2);
         e = hipGetLastError();

@@ -1,5 +1,5 @@
-"""Operator construction at row counts whose 16 lanes per row are more threads
-than one dimension of a launch holds."""
+"""Row and point counts whose lanes are more than one row of a folded grid, or more
+than one dimension of a launch, holds."""
 
 import pytest
 import torch
@@ -32,3 +32,26 @@ def test_pairs(n):
     w[n - 1] = 0.25
     with pytest.raises(gl.GLError, match="symmetric"):
         gl.Operator(i, (i[:-1] ^ 1).to(torch.int32), w, store_w="f32")
+
+
+# a wavefront per query fills one row of the folded grid at 4 * 65 536 points, 26
+# operand vectors per point of 64 coordinates at 645 277
+@pytest.mark.parametrize("n,d,span", [(300_001, 3, 200), (646_000, 64, 200)])
+def test_knn_folded(n, d, span):
+    """Integer coordinates, whose distances are exact: lists with ties to the lower index."""
+    k = 10
+    g = torch.Generator(device=DEV)
+    g.manual_seed(n)
+    x = torch.randint(0, span, (n, d), generator=g, device=DEV).float()
+    idx, d2 = gl.knn(x, k)
+    edge = 4 * 65536
+    rows = [0, 1, edge - 2, edge - 1, edge, edge + 1, 2 * edge, 2 * edge + 1, n - 33, n - 2, n - 1]
+    rows += torch.randint(0, n, (20,), generator=g, device=DEV).tolist()
+    for q in (r for r in rows if r < n):
+        dist = ((x - x[q]) ** 2).sum(1).to(torch.int64)  # whole numbers below 2^24
+        key = dist * n + torch.arange(n, device=DEV)
+        key[q] = 2**62
+        best = torch.sort(torch.topk(key, k, largest=False).values).values
+        assert torch.equal(idx[q].to(torch.int64), best % n), q
+        assert torch.equal(d2[q].to(torch.int64), best // n), q
+    say(f"knn n={n} d={d}: {len(rows)} rows")
