@@ -7,8 +7,9 @@
 // with FMA in coordinate order, ties go to the lower index.  For d <= 64 it is
 // found in two ways.
 //
-// Few points (or a stream under capture): knn_scan_kernel, one wavefront per
-// query over all points, no temporary memory.
+// Few points (or a stream under capture): every query over all points, no temporary
+// memory, by knn_scan_kernel, a wavefront per query or per four, or, when the queries
+// are enough to fill the chip so, by knn_block_kernel, a thread per query.
 //
 // Otherwise the n^2 distances are first formed approximately on the matrix
 // cores, but to nearly f32 accuracy: the centred points are scaled by a power
@@ -20,7 +21,9 @@
 // 16 pairs.  Each lane keeps the T > k smallest approximate values of its
 // query; knn_refine_kernel forms the exact distances of those candidates,
 // takes the k best and proves from the error bound that no other point can
-// enter or tie; queries without that proof are scanned by knn_scan_kernel.
+// enter or tie; queries without that proof (ties at the k-th place, mostly: whole
+// numbers, copies) are scanned by the same two kernels, starting from the k-th
+// distance that their candidates gave.
 // Nothing of size n x n is ever formed, and no step waits for the host.
 //
 // Measured (k = 15, one vector-ALU kernel with a thread per query before): n =
@@ -30,6 +33,7 @@
 // by the vector work on what passes the thresholds.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <string>
 
@@ -361,7 +365,8 @@ __global__ __launch_bounds__(256) void knn_refine_kernel(const float* __restrict
                                                         const float* __restrict__ bound,
                                                         const int32_t* __restrict__ cand,
                                                         int32_t* __restrict__ idx_out, float* __restrict__ d2_out,
-                                                        int32_t* __restrict__ fails, unsigned int* fail_count) {
+                                                        int32_t* __restrict__ fails, float* __restrict__ fail_dk,
+                                                        unsigned int* fail_count) {
     extern __shared__ float2 rsm[];  // [4][2 segs T] (distance, index)
     __shared__ float kth[4];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -412,9 +417,34 @@ __global__ __launch_bounds__(256) void knn_refine_kernel(const float* __restrict
             const float rel = (float)(d + 4) * 0x1.1p-24f;
             ok = (nq + f->inv2 * nu - E) * (1.0f - rel) > dk;
         }
-        if (!ok) fails[atomicAdd(fail_count, 1u)] = (int32_t)q;
+        if (!ok) {
+            const unsigned int slot = atomicAdd(fail_count, 1u);
+            fails[slot] = (int32_t)q;
+            fail_dk[slot] = kth[wave];
+        }
     }
 }
+
+// The queries that are scanned: every point, or a list of *count of them, each with
+// the k-th distance that its candidates gave (infinity when there were too few, or
+// none).  Points beyond that distance cannot be among its k best, points at it can.
+struct KnnRows {
+    const int32_t* rows;        // NULL: every point
+    const float* dk;
+    const unsigned int* count;
+    const KnnFrame* frame;
+    int64_t limit, limit_free;  // queries from which on knn_block_kernel takes them: with the distances, without
+
+    __device__ int64_t total(int64_t n) const { return rows ? (int64_t)*count : n; }
+    __device__ bool many(int64_t m) const { return m >= (rows && !frame->bad ? limit : limit_free); }
+    __device__ int64_t query(int64_t at) const { return rows ? (int64_t)rows[at] : at; }
+    // distances below this are taken: the least float above dk
+    __device__ float start(int64_t at) const {
+        if (!rows) return INFINITY;
+        const uint32_t b = __float_as_uint(dk[at]);  // not negative
+        return __uint_as_float(b < 0x7f800000u ? b + 1u : 0x7f800000u);
+    }
+};
 
 constexpr int kScanPts = 4;                      // points per lane and step
 constexpr int kScanQ = 4;                        // queries per wavefront when there are many
@@ -427,16 +457,15 @@ constexpr int kScanCap = 64 * kScanPts + 64;     // buffered distances per query
 // when it holds more than 64 the k best are kept (by rank among the buffered)
 // and the k-th becomes the threshold.  Points come in increasing order, so a
 // later point tied with the k-th never enters, and a distance that is NaN or
-// infinite is never below the threshold.  rows: the queries, a list of *count
-// entries; every point is one when rows is NULL.
+// infinite is never below the threshold.
 __global__ __launch_bounds__(256) void knn_scan_kernel(const float* __restrict__ x, int64_t n, int32_t d, int32_t k,
-                                                       const int32_t* __restrict__ rows,
-                                                       const unsigned int* __restrict__ count,
-                                                       int32_t* __restrict__ idx_out, float* __restrict__ d2_out) {
+                                                       KnnRows r, int32_t* __restrict__ idx_out,
+                                                       float* __restrict__ d2_out) {
     __shared__ float2 sb[4][kScanQ][kScanCap];
     __shared__ float sq[4][kScanQ][kKnnMaxD];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    const int64_t total = rows ? (int64_t)*count : n;
+    const int64_t total = r.total(n);
+    if (r.many(total)) return;
     const int per = total > 8192 ? kScanQ : 1;
     const int64_t groups = (total + per - 1) / per;
     auto settle = [] { __builtin_amdgcn_wave_barrier(); };  // LDS is in order within a wavefront
@@ -449,9 +478,9 @@ __global__ __launch_bounds__(256) void knn_scan_kernel(const float* __restrict__
         for (int u = 0; u < kScanQ; ++u) {
             const int64_t at = g * per + u;
             const bool on = u < per && at < total;
-            q[u] = on ? (rows ? (int64_t)rows[at] : at) : 0;
+            q[u] = on ? r.query(at) : 0;
             live += on ? 1 : 0;
-            thr[u] = INFINITY;
+            thr[u] = on ? r.start(at) : INFINITY;
             cnt[u] = 0;
             if (lane < d) sq[wave][u][lane] = x[q[u] * d + lane];
         }
@@ -542,10 +571,159 @@ __global__ __launch_bounds__(256) void knn_scan_kernel(const float* __restrict__
     }
 }
 
-hipError_t knn_scan_all(const float* x, int64_t n, int32_t d, int32_t k, int32_t* idx, float* d2, hipStream_t s) {
-    const int64_t blocks = n > 8192 ? (n + 4 * kScanQ - 1) / (4 * kScanQ) : (n + 3) / 4;
-    hipLaunchKernelGGL(knn_scan_kernel, dim3((unsigned)(blocks < (1 << 20) ? blocks : (1 << 20))), dim3(256), 0, s, x, n, d, k,
-                       (const int32_t*)nullptr, (const unsigned int*)nullptr, idx, d2);
+constexpr int kBlockQ = 256;  // queries and threads of a workgroup (64 and 128: more staging per query, up to 1.5 times as long)
+
+template <int D, int KM> struct KnnBlock {
+    static constexpr int points = D <= 20 ? 256 : 128;  // staged at a time: at most 32 KB
+    static constexpr int ahead = D <= 16 && D + KM <= 40 ? 4 : 2;  // points whose distances are formed together
+    // wavefronts per SIMD that the query, its list and one point leave registers for
+    static constexpr int regs = 2 * D + 2 * KM + (D > 40 ? 44 : 24);
+    static constexpr int waves = regs > 168 ? 2 : regs > 128 ? 3 : 4;
+};
+
+// One query per thread, its coordinates and its k best in registers; the points go
+// through LDS and are read as broadcasts, so a pair costs little more than its 2 D
+// vector instructions, which bound it.  Made for many queries: up to one workgroup
+// per CU the time does not depend on their number.  Points come in increasing order,
+// so a later point tied with the k-th never enters.
+template <int D, int KM>
+__global__ __launch_bounds__(kBlockQ, (KnnBlock<D, KM>::waves)) void knn_block_kernel(
+    const float* __restrict__ x, int64_t n, int32_t d, int32_t k, KnnRows r, int32_t* __restrict__ idx_out,
+    float* __restrict__ d2_out) {
+    constexpr int TP = KnnBlock<D, KM>::points, P = KnnBlock<D, KM>::ahead;
+    __shared__ float tile[TP * D];
+    const int64_t total = r.total(n), at = (int64_t)blockIdx.x * kBlockQ + threadIdx.x;
+    if (!r.many(total) || (int64_t)blockIdx.x * kBlockQ >= total) return;
+    const bool active = at < total;
+    const int64_t q = active ? r.query(at) : 0;
+    float qc[D];
+#pragma unroll
+    for (int c = 0; c < D; ++c) qc[c] = c < d ? x[q * d + c] : 0.0f;
+    float best[KM];
+    int32_t bi[KM];
+#pragma unroll
+    for (int i = 0; i < KM; ++i) {
+        best[i] = INFINITY;
+        bi[i] = -1;
+    }
+    float thr = active ? r.start(at) : 0.0f;
+    for (int64_t base = 0; base < n; base += TP) {
+        const int cnt = (int)(n - base < TP ? n - base : TP);
+        __syncthreads();
+        for (int e = threadIdx.x; e < TP * D; e += kBlockQ) {
+            const int p = e / D, c = e - p * D;
+            tile[e] = (p < cnt && c < d) ? x[(base + p) * d + c] : 0.0f;
+        }
+        __syncthreads();
+        for (int p = 0; p < cnt; p += P) {
+            float acc[P];
+#pragma unroll
+            for (int u = 0; u < P; ++u) {
+                acc[u] = 0.0f;
+#pragma unroll
+                for (int c = 0; c < D; ++c) {
+                    const float t = qc[c] - tile[(p + u) * D + c];
+                    acc[u] = fmaf(t, t, acc[u]);
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < P; ++u) {
+                const int64_t j = base + p + u;
+                if (acc[u] < thr && j != q && p + u < cnt) {
+                    // insert after every entry <= acc and shift the rest down one place
+                    // (descending i reads each old entry before it is overwritten)
+#pragma unroll
+                    for (int i = KM - 1; i >= 1; --i) {
+                        const bool shift = acc[u] < best[i - 1], here = acc[u] < best[i];
+                        best[i] = shift ? best[i - 1] : (here ? acc[u] : best[i]);
+                        bi[i] = shift ? bi[i - 1] : (here ? (int32_t)j : bi[i]);
+                    }
+                    if (acc[u] < best[0]) {
+                        best[0] = acc[u];
+                        bi[0] = (int32_t)j;
+                    }
+                    float t = best[0];
+#pragma unroll
+                    for (int i = 1; i < KM; ++i) t = (i == k - 1) ? best[i] : t;
+                    thr = fminf(thr, t);
+                }
+            }
+        }
+    }
+    if (!active) return;
+#pragma unroll
+    for (int i = 0; i < KM; ++i) {
+        if (i < k) {
+            idx_out[q * k + i] = bi[i];
+            if (d2_out) d2_out[q * k + i] = best[i];
+        }
+    }
+}
+
+template <int D, int KM>
+void knn_block_launch_t(const float* x, int64_t n, int32_t d, int32_t k, const KnnRows& r, int32_t* idx, float* d2,
+                        hipStream_t s) {
+    hipLaunchKernelGGL((knn_block_kernel<D, KM>), dim3((unsigned)((n + kBlockQ - 1) / kBlockQ)), dim3(kBlockQ), 0, s, x, n,
+                       d, k, r, idx, d2);
+}
+
+template <int D>
+void knn_block_launch_d(const float* x, int64_t n, int32_t d, int32_t k, const KnnRows& r, int32_t* idx, float* d2,
+                        hipStream_t s) {
+    if (k <= 8) knn_block_launch_t<D, 8>(x, n, d, k, r, idx, d2, s);
+    else if (k <= 16) knn_block_launch_t<D, 16>(x, n, d, k, r, idx, d2, s);
+    else if (k <= 24) knn_block_launch_t<D, 24>(x, n, d, k, r, idx, d2, s);
+    else knn_block_launch_t<D, 32>(x, n, d, k, r, idx, d2, s);
+}
+
+void knn_block_launch(const float* x, int64_t n, int32_t d, int32_t k, const KnnRows& r, int32_t* idx, float* d2,
+                      hipStream_t s) {
+    switch (d) {
+#define GL_KNN_D(DD) \
+    case DD:         \
+        return knn_block_launch_d<DD>(x, n, d, k, r, idx, d2, s);
+        GL_KNN_D(1) GL_KNN_D(2) GL_KNN_D(3) GL_KNN_D(4) GL_KNN_D(5) GL_KNN_D(6) GL_KNN_D(7) GL_KNN_D(8)
+        GL_KNN_D(9) GL_KNN_D(10) GL_KNN_D(11) GL_KNN_D(12) GL_KNN_D(13) GL_KNN_D(14) GL_KNN_D(15)
+        GL_KNN_D(16)
+#undef GL_KNN_D
+        default:
+            break;
+    }
+    // wider features: padded to the next width with zero coordinates
+    if (d <= 20) return knn_block_launch_d<20>(x, n, d, k, r, idx, d2, s);
+    if (d <= 24) return knn_block_launch_d<24>(x, n, d, k, r, idx, d2, s);
+    if (d <= 28) return knn_block_launch_d<28>(x, n, d, k, r, idx, d2, s);
+    if (d <= 32) return knn_block_launch_d<32>(x, n, d, k, r, idx, d2, s);
+    if (d <= 40) return knn_block_launch_d<40>(x, n, d, k, r, idx, d2, s);
+    if (d <= 48) return knn_block_launch_d<48>(x, n, d, k, r, idx, d2, s);
+    if (d <= 56) return knn_block_launch_d<56>(x, n, d, k, r, idx, d2, s);
+    return knn_block_launch_d<64>(x, n, d, k, r, idx, d2, s);
+}
+
+// Queries from which on knn_block_kernel is the faster of the two, whose time does
+// not depend on their number up to some 65 000.  With a k-th distance to start from
+// (100 000 points, k = 15, scan / block in ms without the 1.7 to 7.2 of the products):
+// d = 2: 30 000 queries 3.6 / 5.8, 60 000 7.5 / 6.3; d = 10: 7.6 / 11.1 and 15.4 / 11.4;
+// d = 27: 16 000 11.1 / 21.9, 30 000 23.9 / 21.9; d = 64: 19.8 / 41.9 and 43.1 / 41.9.
+int64_t knn_block_min_listed(int32_t d) { return d <= 3 ? 48000 : d <= 16 ? 40000 : 28000; }
+
+// Without one (every point, k = 15): d = 3: 65 000 points 5.2 / 4.9, k = 32: 100 000
+// 13.4 / 14.1; d = 10: 48 000 4.4 / 5.7, 65 000 8.0 / 7.5; d = 27: 32 000 6.5 / 7.3,
+// 48 000 14.2 / 11.0; d = 64: 13.7 / 15.2 and 28.9 / 21.9.
+int64_t knn_block_min(int32_t d, int32_t k) { return d > 16 ? 36000 : d <= 3 && k > 16 ? 110000 : 60000; }
+
+// The queries of r by whichever of the two kernels they are enough for: known here
+// for every point, on the device for a list.
+hipError_t knn_scan(const float* x, int64_t n, int32_t d, int32_t k, KnnRows r, int32_t* idx, float* d2, hipStream_t s) {
+    r.limit = knn_block_min_listed(d);
+    r.limit_free = knn_block_min(d, k);
+    const bool block = n >= (r.rows ? std::min(r.limit, r.limit_free) : r.limit_free);
+    if (r.rows || !block) {
+        const int64_t blocks = r.rows ? 1024 : n > 8192 ? (n + 4 * kScanQ - 1) / (4 * kScanQ) : (n + 3) / 4;
+        hipLaunchKernelGGL(knn_scan_kernel, dim3((unsigned)std::min<int64_t>(blocks, 1 << 20)), dim3(256), 0, s, x, n, d,
+                           k, r, idx, d2);
+    }
+    if (block) knn_block_launch(x, n, d, k, r, idx, d2, s);
     return hipGetLastError();
 }
 
@@ -579,7 +757,8 @@ hipError_t knn_launch(const float* x, int64_t n, int32_t d, int32_t k, int32_t* 
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     hipError_t e = hipStreamIsCapturing(s, &cap);
     if (e != hipSuccess) return e;
-    if (n * (d + 10) <= kKnnScanMax || d == 1 || cap != hipStreamCaptureStatusNone) return knn_scan_all(x, n, d, k, idx, d2, s);
+    if (n * (d + 10) <= kKnnScanMax || d == 1 || cap != hipStreamCaptureStatusNone)
+        return knn_scan(x, n, d, k, KnnRows{}, idx, d2, s);
     const int32_t tiles = (int32_t)((n + 31) / 32);
     const int64_t np = (int64_t)tiles * 32;
     const int32_t T = k <= 4 ? 8 : k <= 8 ? 12 : k <= 12 ? 16 : k <= 16 ? 20 : k <= 20 ? 24 : k <= 28 ? 32 : 36;
@@ -592,10 +771,10 @@ hipError_t knn_launch(const float* x, int64_t n, int32_t d, int32_t k, int32_t* 
                  b_sum = al((size_t)kStatBlocks * kKnnMaxD * 8), b_mm = al((size_t)kStatBlocks * kKnnMaxD * 4),
                  b_frame = al(sizeof(KnnFrame)) + 256;
     char* base = nullptr;
-    if (hipMallocAsync((void**)&base, b_frag + b_norm + b_cand + b_bound + b_fail + b_sum + 2 * b_mm + b_frame, s) !=
+    if (hipMallocAsync((void**)&base, b_frag + b_norm + b_cand + b_bound + 2 * b_fail + b_sum + 2 * b_mm + b_frame, s) !=
         hipSuccess) {
         (void)hipGetLastError();
-        return knn_scan_all(x, n, d, k, idx, d2, s);
+        return knn_scan(x, n, d, k, KnnRows{}, idx, d2, s);
     }
     char* p = base;
     auto take = [&](size_t b) { char* r = p; p += b; return r; };
@@ -604,6 +783,7 @@ hipError_t knn_launch(const float* x, int64_t n, int32_t d, int32_t k, int32_t* 
     int32_t* cand = (int32_t*)take(b_cand);
     float* bound = (float*)take(b_bound);
     int32_t* fails = (int32_t*)take(b_fail);
+    float* fail_dk = (float*)take(b_fail);
     double* psum = (double*)take(b_sum);
     float* pmin = (float*)take(b_mm);
     float* pmax = (float*)take(b_mm);
@@ -628,10 +808,16 @@ hipError_t knn_launch(const float* x, int64_t n, int32_t d, int32_t k, int32_t* 
         const Fold fr = fold_blocks((n + 3) / 4);
         hipLaunchKernelGGL(knn_refine_kernel, dim3(fr.x, fr.y), dim3(256), (size_t)4 * 2 * segs * T * 8, s, x, n, d, k,
                            (const KnnFrame*)f, (const float*)half_norm, segs, T, (const float*)bound,
-                           (const int32_t*)cand, idx, d2, fails, fail_count);
-        hipLaunchKernelGGL(knn_scan_kernel, dim3(1024), dim3(256), 0, s, x, n, d, k,
-                           (const int32_t*)fails, (const unsigned int*)fail_count, idx, d2);
+                           (const int32_t*)cand, idx, d2, fails, fail_dk, fail_count);
         e = hipGetLastError();
+    }
+    if (e == hipSuccess) {
+        KnnRows r{};
+        r.rows = fails;
+        r.dk = fail_dk;
+        r.count = fail_count;
+        r.frame = f;
+        e = knn_scan(x, n, d, k, r, idx, d2, s);
     }
     const hipError_t ef = hipFreeAsync(base, s);
     return e != hipSuccess ? e : ef;

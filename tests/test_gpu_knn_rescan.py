@@ -1,0 +1,81 @@
+"""gl_knn for d <= 64 where queries have no proof, or the matrix cores are not used:
+the scans of many queries, on both sides of the counts where a thread per query
+takes over from a wavefront per query.  Coordinates are small whole numbers, so
+every distance is an exact float32 integer and the lists, ties to the lower
+index included, must equal the reference's."""
+
+import numpy as np
+import pytest
+import torch
+
+import paper_2303_14495_amd as gl
+from tests.gpu_helpers import DEV, say
+
+pytestmark = pytest.mark.gpu
+
+
+def _points(n, d, tied, seed):
+    """`tied` points in groups of 60 copies, the others with coordinates below 200."""
+    rng = np.random.default_rng(seed)
+    x = rng.integers(0, 200, (n, d)).astype(np.float32)
+    x[:tied] = x[np.arange(tied) // 60]
+    return torch.from_numpy(x[rng.permutation(n)]).to(DEV)
+
+
+def _reference(x, k, rows):
+    """Exact lists of the query rows: (distance, index) sorted as whole numbers, on the GPU in float64."""
+    n = x.shape[0]
+    xd = x.double()
+    out_i, out_d = [], []
+    for q in rows:
+        dist = ((xd - xd[q]) ** 2).sum(1)
+        key = torch.where(torch.isfinite(dist), dist, torch.full_like(dist, 2.0**40)).to(torch.int64) * n + torch.arange(n, device=DEV)
+        key[q] = 2**62
+        best = torch.sort(torch.topk(key, k, largest=False).values).values
+        out_i.append(best % n)
+        out_d.append(best // n)
+    return torch.stack(out_i), torch.stack(out_d)
+
+
+def _check(x, k, idx, d2, seed):
+    n = x.shape[0]
+    rows = sorted(set(np.random.default_rng(seed).choice(n, 60, replace=False).tolist() + [0, 63, 64, 255, 256, n - 2, n - 1]))
+    rows = [q for q in rows if bool(torch.isfinite(x[q]).all())]
+    want_i, want_d = _reference(x, k, rows)
+    assert torch.equal(idx[rows].to(torch.int64), want_i)
+    assert torch.equal(d2[rows].to(torch.int64), want_d)
+
+
+# listed queries: the limits are 48 000 (d <= 3), 40 000 (d <= 16) and 28 000; k at the
+# edges of the register lists (8, 16, 24, 32); d below, at and between the widths
+@pytest.mark.parametrize("n,d,k,tied", [
+    (49000, 2, 8, 47940), (49000, 3, 9, 48060), (41000, 4, 16, 39960), (41001, 7, 17, 40080), (40100, 16, 32, 40080),
+    (28100, 17, 24, 28020), (28200, 20, 25, 28020), (28300, 21, 15, 27960), (29000, 27, 10, 28980), (28500, 33, 5, 28500),
+    (28500, 41, 20, 28500), (28500, 49, 30, 28500), (28500, 57, 16, 28500), (28500, 64, 32, 28440), (30000, 64, 8, 600)])
+def test_listed_queries(n, d, k, tied):
+    say(f"knn n={n} d={d} k={k}, {tied} points in copies")
+    x = _points(n, d, tied, n + d)
+    idx, d2 = gl.knn(x, k)
+    _check(x, k, idx, d2, d)
+
+
+# every point: the limits are 110 000 (d <= 3 and k > 16), 60 000 (d <= 16) and 36 000; under
+# capture, where nothing may be allocated, and with a coordinate that is no number
+@pytest.mark.parametrize("n,d,k", [(110001, 1, 17), (109999, 3, 20), (60001, 3, 16), (59999, 10, 4), (60300, 15, 25),
+                                   (36001, 17, 8), (35999, 27, 32), (36500, 40, 12), (36001, 64, 32)])
+@pytest.mark.parametrize("capture", [False, True])
+def test_every_point(n, d, k, capture):
+    say(f"knn n={n} d={d} k={k} capture={capture}")
+    x = _points(n, d, 6000, n + k)
+    if capture:
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            idx, d2 = gl.knn(x, k)
+        graph.replay()
+        torch.cuda.synchronize()
+    else:
+        x[77, d - 1] = float("nan")
+        idx, d2 = gl.knn(x, k)
+        assert bool((idx[77] == -1).all()) and bool(torch.isinf(d2[77]).all())
+        assert not bool((idx == 77).any())
+    _check(x, k, idx, d2, k)
