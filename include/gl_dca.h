@@ -533,6 +533,14 @@ gl_status gl_server_destroy(gl_server *srv);
 gl_status gl_knn(const float *x, int64_t n, int32_t d, int32_t k, int32_t *idx_out,
                  float *d2_out, void *stream);
 
+/* gl_knn for any d, telling how it went: as if an allocation of more than
+ * `temp_bytes` of temporaries failed, and *rescanned (host out) = the queries
+ * whose neighbours came from a scan of all points: those without a proof, or
+ * all n where the matrix cores were not used.  Lists as gl_knn's.
+ * Synchronises `stream`. */
+gl_status gl_knn_bounded(const float *x, int64_t n, int32_t d, int32_t k, int32_t *idx_out,
+                         float *d2_out, size_t temp_bytes, int64_t *rescanned, void *stream);
+
 /* Host: queries of the calling thread's last gl_knn call with d > 64 that
  * needed the exact rescan (0 after a call with d <= 64, -1 after an error). */
 int64_t gl_knn_fallback_rows(void);

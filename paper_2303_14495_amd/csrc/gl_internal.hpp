@@ -130,8 +130,9 @@ hipError_t launch_window_power(const gl_operator* op, const float* x, float* y, 
                                float* partials, float* part, hipStream_t s);
 
 // gl_knn for 64 < d <= 4096 (arguments checked by the caller); *fallback_rows
-// receives the number of rows recomputed by the exact scan.
-gl_status knn_wide(const float* x, int64_t n, int32_t d, int32_t k, int32_t* idx_out, float* d2_out,
+// receives the number of rows recomputed by the exact scan; limit: an allocation of
+// more temporary bytes counts as failed.
+gl_status knn_wide(const float* x, int64_t n, int32_t d, int32_t k, int32_t* idx_out, float* d2_out, size_t limit,
                    hipStream_t s, int64_t* fallback_rows);
 
 // LDS bytes one window-layout block needs for K columns of accumulator size acc.

@@ -753,7 +753,11 @@ hipError_t knn_tile_launch(const float* x, int64_t n, int32_t d, int32_t T, int3
 
 // One coordinate is scanned: near neighbours on a line are closer than the
 // approximate distances can tell apart, and most queries would be scanned anyway.
-hipError_t knn_launch(const float* x, int64_t n, int32_t d, int32_t k, int32_t* idx, float* d2, hipStream_t s) {
+// limit: an allocation of more bytes counts as failed.  rescanned (or NULL, and then
+// nothing waits): the queries scanned over all points.
+hipError_t knn_launch(const float* x, int64_t n, int32_t d, int32_t k, int32_t* idx, float* d2, size_t limit,
+                      int64_t* rescanned, hipStream_t s) {
+    if (rescanned) *rescanned = n;
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     hipError_t e = hipStreamIsCapturing(s, &cap);
     if (e != hipSuccess) return e;
@@ -770,9 +774,9 @@ hipError_t knn_launch(const float* x, int64_t n, int32_t d, int32_t k, int32_t* 
                  b_cand = al((size_t)n * 2 * segs * T * 4), b_bound = al((size_t)n * segs * 4), b_fail = al((size_t)n * 4),
                  b_sum = al((size_t)kStatBlocks * kKnnMaxD * 8), b_mm = al((size_t)kStatBlocks * kKnnMaxD * 4),
                  b_frame = al(sizeof(KnnFrame)) + 256;
+    const size_t total = b_frag + b_norm + b_cand + b_bound + 2 * b_fail + b_sum + 2 * b_mm + b_frame;
     char* base = nullptr;
-    if (hipMallocAsync((void**)&base, b_frag + b_norm + b_cand + b_bound + 2 * b_fail + b_sum + 2 * b_mm + b_frame, s) !=
-        hipSuccess) {
+    if (total > limit || hipMallocAsync((void**)&base, total, s) != hipSuccess) {
         (void)hipGetLastError();
         return knn_scan(x, n, d, k, KnnRows{}, idx, d2, s);
     }
@@ -819,6 +823,12 @@ hipError_t knn_launch(const float* x, int64_t n, int32_t d, int32_t k, int32_t* 
         r.frame = f;
         e = knn_scan(x, n, d, k, r, idx, d2, s);
     }
+    if (e == hipSuccess && rescanned) {
+        unsigned int listed = 0;
+        e = hipMemcpyAsync(&listed, fail_count, sizeof(listed), hipMemcpyDeviceToHost, s);
+        if (e == hipSuccess) e = hipStreamSynchronize(s);
+        *rescanned = listed;
+    }
     const hipError_t ef = hipFreeAsync(base, s);
     return e != hipSuccess ? e : ef;
 }
@@ -832,8 +842,8 @@ thread_local int64_t g_knn_fallback = 0;
 
 extern "C" int64_t gl_knn_fallback_rows(void) { return g_knn_fallback; }
 
-extern "C" gl_status gl_knn(const float* x, int64_t n, int32_t d, int32_t k, int32_t* idx_out, float* d2_out,
-                            void* stream) {
+static gl_status knn_call(const float* x, int64_t n, int32_t d, int32_t k, int32_t* idx_out, float* d2_out, size_t limit,
+                          int64_t* rescanned, void* stream) {
     if (!x || !idx_out) {
         gl::set_last_error("x and idx_out must not be NULL");
         return GL_E_INVALID_ARG;
@@ -852,15 +862,35 @@ extern "C" gl_status gl_knn(const float* x, int64_t n, int32_t d, int32_t k, int
     }
     if (d > 64) {
         int64_t fb = 0;
-        const gl_status st = gl::knn_wide(x, n, d, k, idx_out, d2_out, (hipStream_t)stream, &fb);
+        const gl_status st = gl::knn_wide(x, n, d, k, idx_out, d2_out, limit, (hipStream_t)stream, &fb);
         g_knn_fallback = st == GL_OK ? fb : -1;
+        if (rescanned) *rescanned = fb;
         return st;
     }
     g_knn_fallback = 0;
-    const hipError_t e = gl::knn_launch(x, n, d, k, idx_out, d2_out, (hipStream_t)stream);
+    const hipError_t e = gl::knn_launch(x, n, d, k, idx_out, d2_out, limit, rescanned, (hipStream_t)stream);
     if (e != hipSuccess) {
         gl::set_last_error(std::string("knn launch: ") + hipGetErrorString(e));
         return GL_E_HIP;
     }
     return GL_OK;
+}
+
+extern "C" gl_status gl_knn(const float* x, int64_t n, int32_t d, int32_t k, int32_t* idx_out, float* d2_out,
+                            void* stream) {
+    return knn_call(x, n, d, k, idx_out, d2_out, SIZE_MAX, nullptr, stream);
+}
+
+extern "C" gl_status gl_knn_bounded(const float* x, int64_t n, int32_t d, int32_t k, int32_t* idx_out, float* d2_out,
+                                    size_t temp_bytes, int64_t* rescanned, void* stream) {
+    if (!rescanned) {
+        gl::set_last_error("rescanned must not be NULL");
+        return GL_E_INVALID_ARG;
+    }
+    const gl_status st = knn_call(x, n, d, k, idx_out, d2_out, temp_bytes, rescanned, stream);
+    if (st == GL_OK && hipStreamSynchronize((hipStream_t)stream) != hipSuccess) {
+        gl::set_last_error("knn");
+        return GL_E_HIP;
+    }
+    return st;
 }

@@ -667,7 +667,7 @@ __global__ __launch_bounds__(64) void kw_scan_merge_kernel(int32_t k, int32_t sl
 namespace gl {
 
 // Wide-feature path of gl_knn; arguments already checked (64 < d <= 4096).
-gl_status knn_wide(const float* x, int64_t n, int32_t d, int32_t k, int32_t* idx_out, float* d2_out,
+gl_status knn_wide(const float* x, int64_t n, int32_t d, int32_t k, int32_t* idx_out, float* d2_out, size_t limit,
                    hipStream_t s, int64_t* fallback_rows) {
     const int32_t dp = (d + kWStep - 1) / kWStep * kWStep, ns = dp / kWStep;
     KwPlan plan;
@@ -685,7 +685,8 @@ gl_status knn_wide(const float* x, int64_t n, int32_t d, int32_t k, int32_t* idx
                  b_c = al((size_t)plan.first_list(n) * T * 8), b_f = al((size_t)n * 4);
     const size_t b_mu = al((size_t)d * 4) + al((size_t)kMeanSlices * d * 8);
     char* base = nullptr;
-    if (hipMallocAsync((void**)&base, b_xh + b_n + b_cn + b_c + b_f + b_mu + 256, s) != hipSuccess) {
+    const size_t total = b_xh + b_n + b_cn + b_c + b_f + b_mu + 256;
+    if (total > limit || hipMallocAsync((void**)&base, total, s) != hipSuccess) {
         (void)hipGetLastError();
         return wfail(GL_E_NOMEM, "temporary device memory for the wide kNN");
     }

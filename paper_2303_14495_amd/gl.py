@@ -117,6 +117,8 @@ SIGNATURES = {
     "gl_server_info": (ctypes.c_int, [_P, _P, _P, _P, _P, _P]),
     "gl_server_destroy": (ctypes.c_int, [_P]),
     "gl_knn": (ctypes.c_int, [_P, ctypes.c_int64, ctypes.c_int32, ctypes.c_int32, _P, _P, _P]),
+    "gl_knn_bounded": (ctypes.c_int, [_P, ctypes.c_int64, ctypes.c_int32, ctypes.c_int32, _P, _P,
+                                      ctypes.c_size_t, _P, _P]),
     "gl_second_eigenpair_workspace_size": (ctypes.c_int, [_P, ctypes.c_int32, _P]),
     "gl_second_eigenpair": (ctypes.c_int, [_P, ctypes.c_int32, ctypes.c_int32, ctypes.c_double, _P,
                                            _P, _P, ctypes.c_size_t, _P, _P, _P, _P]),
@@ -441,6 +443,22 @@ def knn(x: torch.Tensor, k: int, with_distances: bool = True, stream=None):
     _check(load_library().gl_knn(_ptr(x), n, d, k, _ptr(idx), _ptr(d2) if d2 is not None else None,
                                  _stream_handle(stream)))
     return idx, d2
+
+
+def knn_bounded(x: torch.Tensor, k: int, temp_bytes: int | None = None, stream=None):
+    """knn() with its temporary device memory bounded (None: not), also returning
+    the number of queries that were scanned over all points."""
+    if x.dtype != torch.float32 or x.dim() != 2 or not x.is_cuda:
+        raise GLError(1, "x must be a device float32 [n, d] tensor")
+    x = x.contiguous()
+    n, d = x.shape
+    idx = torch.empty((n, k), dtype=torch.int32, device=x.device)
+    d2 = torch.empty((n, k), dtype=torch.float32, device=x.device)
+    scanned = ctypes.c_int64()
+    limit = ctypes.c_size_t(-1).value if temp_bytes is None else temp_bytes
+    _check(load_library().gl_knn_bounded(_ptr(x), n, d, k, _ptr(idx), _ptr(d2), limit,
+                                         ctypes.byref(scanned), _stream_handle(stream)))
+    return idx, d2, scanned.value
 
 
 class Server:

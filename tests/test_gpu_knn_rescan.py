@@ -79,3 +79,49 @@ def test_every_point(n, d, k, capture):
         assert bool((idx[77] == -1).all()) and bool(torch.isinf(d2[77]).all())
         assert not bool((idx == 77).any())
     _check(x, k, idx, d2, k)
+
+
+def _mixture(n, d, seed):
+    g = torch.Generator(device=DEV)
+    g.manual_seed(seed)
+    means = 3.0 * torch.randn(5, d, generator=g, device=DEV)
+    return means[torch.randint(0, 5, (n,), generator=g, device=DEV)] + torch.randn(n, d, generator=g, device=DEV)
+
+
+# one case per k-step count and list length of the matrix path, and several segments.
+# The error bound is about 4e-5 |q|^2 at d = 64 and 3e-6 |q|^2 at d = 2; the T-th of a
+# query's approximate distances lies at least 4 places behind the k-th, a gap of
+# 0.5 % of the distance or more at these sizes, so all but stray queries have a proof.
+@pytest.mark.parametrize("n,d,k", [(6001, 4, 4), (5857, 10, 8), (6015, 15, 12), (5000, 20, 16), (4001, 31, 20), (3001, 42, 28),
+                                   (2500, 64, 31), (20000, 3, 10), (70000, 10, 15)])
+def test_matrix_path_answers(n, d, k):
+    """General coordinates: nearly every query's list comes from the matrix path, and
+    is the one of a scan of all points, bit for bit."""
+    x = _mixture(n, d, n)
+    idx, d2, scanned = gl.knn_bounded(x, k)
+    say(f"knn n={n} d={d} k={k}: {scanned} queries scanned")
+    assert scanned <= n // 50
+    si, sd, every = gl.knn_bounded(x, k, temp_bytes=1)
+    assert every == n
+    assert torch.equal(idx, si) and torch.equal(d2, sd)
+    gi, gd = gl.knn(x, k)
+    assert torch.equal(idx, gi) and torch.equal(d2, gd)
+
+
+def test_ties_are_scanned():
+    """Copies at the k-th place: their queries, at least, have no proof (a point whose k-th
+    neighbour is a copy has none either)."""
+    n, tied = 9000, 6000
+    _, _, scanned = gl.knn_bounded(_points(n, 5, tied, 3), 12)
+    say(f"{scanned} of {n} queries scanned, {tied} points in copies")
+    assert tied <= scanned <= n
+
+
+def test_bounded_arguments():
+    x = _mixture(500, 3, 1)
+    with pytest.raises(gl.GLError):
+        gl.knn_bounded(x, 0)
+    with pytest.raises(gl.GLError):
+        gl.knn_bounded(x.double(), 3)
+    assert gl.knn_bounded(x, 3)[2] == 500  # few points: scanned
+    assert gl.knn_bounded(_mixture(1000, 80, 2), 5)[2] <= 50  # wide: rescans of the certificate
