@@ -187,24 +187,41 @@ constexpr int kWMaxSegs = 16;
 constexpr int kWMaxCand = 768;       // candidates of a query: 4 kWMaxSegs lists of 12
 constexpr size_t kWLds = (size_t)3 * kWStage * 16 + (size_t)kWHits * kWThreads * 8 + (size_t)2 * kWB * 4;
 
-// How the (query block, point segment) pairs are dealt to workgroups.  Full rounds
-// of 64 query blocks x 4 segments: the 32 workgroups of an XCD (blockIdx % 8) hold 8
-// query blocks, each read by 4 of them, and 4 segments, each read by 8, so that
-// its L2 serves most of the operands' reads.  The query blocks left over are cut
-// into seg_r segments to fill the chip once more (16 at most: a segment has 4
-// lists of candidates per query).
+// How the (query block, point segment) pairs of one pass are dealt to workgroups.
+// Full rounds of 64 query blocks x 4 segments: the 32 workgroups of an XCD
+// (blockIdx % 8) hold 8 query blocks, each read by 4 of them, and 4 segments, each
+// read by 8, so that its L2 serves most of the operands' reads.  The query blocks
+// left over are cut into seg_r segments to fill the chip once more (16 at most: a
+// segment has 4 lists of candidates per query).  One pass takes all query blocks
+// unless their lists cannot be allocated.
 struct KwPlan {
-    int32_t nblk;   // blocks of kWB points = query blocks
-    int32_t full;   // query blocks in full rounds
+    int32_t nblk;   // blocks of kWB points
+    int32_t first;  // first query block of the pass
+    int32_t nq;     // its query blocks
+    int32_t full;   // those of them in full rounds
     int32_t seg_r;  // segments of the others
-    __host__ __device__ int32_t per() const { return ((nblk - full) * seg_r + 7) / 8; }
+    __host__ __device__ int32_t per() const { return ((nq - full) * seg_r + 7) / 8; }
     __host__ __device__ uint32_t blocks() const { return (uint32_t)full * kWSegs + 8u * (uint32_t)per(); }
+    // lists of query q of the pass (q = 0: its first)
     __host__ __device__ int32_t lists(int64_t q) const { return 4 * (q < (int64_t)full * kWB ? kWSegs : seg_r); }
     __host__ __device__ int64_t first_list(int64_t q) const {
         const int64_t nf = (int64_t)full * kWB;
         return q < nf ? q * 4 * kWSegs : nf * 4 * kWSegs + (q - nf) * 4 * seg_r;
     }
 };
+
+KwPlan kw_plan(int32_t nblk, int32_t first, int32_t nq) {
+    KwPlan p{nblk, first, nq, nq / kWRound * kWRound, 1};
+    const int32_t rest = nq - p.full;
+    if (rest) p.seg_r = std::max(kWSegs, std::min(std::min(kWMaxSegs, nblk), 256 / rest));
+    return p;
+}
+
+// Most lists of the passes of `step` query blocks each.
+int64_t kw_lists(int32_t nblk, int32_t step) {
+    const KwPlan p = kw_plan(nblk, 0, step), last = kw_plan(nblk, 0, nblk % step);
+    return std::max(p.first_list((int64_t)step * kWB), last.first_list((int64_t)last.nq * kWB));
+}
 
 // One 256 x 256 block of products per step of the tile loop.  Wavefront w computes
 // points 128 (w / 4) .. by queries 64 (w % 4) .. with 4 x 2 MFMA tiles of 32 x 32
@@ -244,7 +261,7 @@ __global__ __launch_bounds__(kWThreads) __attribute__((amdgpu_waves_per_eu(2, 2)
         nseg = kWSegs;
     } else {
         const int i = (int)blockIdx.x - plan.full * kWSegs, item = (i & 7) * plan.per() + (i >> 3);
-        if (i >= 8 * plan.per() || item >= (plan.nblk - plan.full) * plan.seg_r) return;
+        if (i >= 8 * plan.per() || item >= (plan.nq - plan.full) * plan.seg_r) return;
         qb = __builtin_amdgcn_readfirstlane(plan.full + item / plan.seg_r);
         seg = __builtin_amdgcn_readfirstlane(item % plan.seg_r);
         nseg = plan.seg_r;
@@ -260,7 +277,7 @@ __global__ __launch_bounds__(kWThreads) __attribute__((amdgpu_waves_per_eu(2, 2)
 
     // staging: wavefront w copies operand tile w of the points and of the queries, 1 KB per instruction
     const int64_t tile_v = (int64_t)ns * 128;  // vectors of an operand tile
-    const kw_h8* qsrc = xp + ((int64_t)qb * 8 + wave) * tile_v;
+    const kw_h8* qsrc = xp + ((int64_t)(plan.first + qb) * 8 + wave) * tile_v;
     const kw_h8* psrc = xp + ((int64_t)b0 * 8 + wave) * tile_v;
     int fb = b0, fs = 0;  // block and step of the next request; past the end the last block is read again
     kw_h8 r0, r1, r2, r3;
@@ -299,7 +316,7 @@ __global__ __launch_bounds__(kWThreads) __attribute__((amdgpu_waves_per_eu(2, 2)
             bv[c][t] = -INFINITY;
             bj[c][t] = 0x7fffffffu;
         }
-    const int64_t q0 = (int64_t)qb * kWB + wq * 64 + (lane & 31);
+    const int64_t q0 = (int64_t)(plan.first + qb) * kWB + wq * 64 + (lane & 31);
 
     fetch();
     put(0);
@@ -400,7 +417,7 @@ __global__ __launch_bounds__(kWThreads) __attribute__((amdgpu_waves_per_eu(2, 2)
     for (int c = 0; c < 2; ++c) {
         const int64_t q = q0 + 32 * c;
         if (q >= n) continue;
-        uint2* out = cand + (plan.first_list(q) + seg * 4 + wp * 2 + (lane >> 5)) * T;
+        uint2* out = cand + (plan.first_list(q - (int64_t)plan.first * kWB) + seg * 4 + wp * 2 + (lane >> 5)) * T;
 #pragma unroll
         for (int t = 0; t < T; ++t) out[t] = make_uint2(__float_as_uint(bv[c][t]), bj[c][t]);
     }
@@ -495,10 +512,10 @@ __global__ __launch_bounds__(256) void kw_refine_kernel(const float* __restrict_
                                                        int32_t* fail_list, unsigned int* fail_count) {
     __shared__ int32_t chosen[4][64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int64_t q = (int64_t)blockIdx.x * 4 + wave;
-    if (q >= n) return;
-    const int total = plan.lists(q) * T, own = (total + 63) / 64;
-    const uint2* cq = cand + plan.first_list(q) * T;
+    const int64_t local = (int64_t)blockIdx.x * 4 + wave, q = (int64_t)plan.first * kWB + local;
+    if (q >= n || local >= (int64_t)plan.nq * kWB) return;
+    const int total = plan.lists(local) * T, own = (total + 63) / 64;
+    const uint2* cq = cand + plan.first_list(local) * T;
     const float nq = norm2[q];
     const float eq = err_a * sqrtf(nq) + err_b * nq + err_c;
     uint32_t key[kWOwn];
@@ -670,25 +687,29 @@ namespace gl {
 gl_status knn_wide(const float* x, int64_t n, int32_t d, int32_t k, int32_t* idx_out, float* d2_out, size_t limit,
                    hipStream_t s, int64_t* fallback_rows) {
     const int32_t dp = (d + kWStep - 1) / kWStep * kWStep, ns = dp / kWStep;
-    KwPlan plan;
-    plan.nblk = (int32_t)((n + kWB - 1) / kWB);
-    plan.full = plan.nblk / kWRound * kWRound;
-    const int32_t rest = plan.nblk - plan.full;
-    plan.seg_r = rest ? std::max(kWSegs, std::min(std::min(kWMaxSegs, plan.nblk), 256 / rest)) : 1;
+    const int32_t nblk = (int32_t)((n + kWB - 1) / kWB);
     // A list must not be expected to hold more than T of the nearest points: 16
     // lists of 8 bound what they leave out by about the 50th nearest point, 16 of 12
     // by the 100th.
     const int32_t T = k <= 12 ? 8 : 12;
-    const int64_t np = (int64_t)plan.nblk * kWB;
+    const int64_t np = (int64_t)nblk * kWB;
     auto al = [](size_t b) { return (b + 255) & ~(size_t)255; };
     const size_t b_xh = al((size_t)np * dp * 2), b_n = al((size_t)n * 4), b_cn = al((size_t)np * 4),
-                 b_c = al((size_t)plan.first_list(n) * T * 8), b_f = al((size_t)n * 4);
+                 b_f = al((size_t)n * 4);
     const size_t b_mu = al((size_t)d * 4) + al((size_t)kMeanSlices * d * 8);
+    // The lists take 1024 or 1536 bytes per query, several times that below 16 384
+    // points: where they cannot be had, the query blocks are taken in passes, each
+    // half as many as the last try, down to one block.
     char* base = nullptr;
-    const size_t total = b_xh + b_n + b_cn + b_c + b_f + b_mu + 256;
-    if (total > limit || hipMallocAsync((void**)&base, total, s) != hipSuccess) {
+    int32_t step = nblk;
+    size_t b_c = 0;
+    for (;; step = (step + 1) / 2) {
+        b_c = al((size_t)kw_lists(nblk, step) * T * 8);
+        const size_t total = b_xh + b_n + b_cn + b_c + b_f + b_mu + 256;
+        if (total <= limit && hipMallocAsync((void**)&base, total, s) == hipSuccess) break;
         (void)hipGetLastError();
-        return wfail(GL_E_NOMEM, "temporary device memory for the wide kNN");
+        base = nullptr;
+        if (step == 1) return wfail(GL_E_NOMEM, "temporary device memory for the wide kNN");
     }
     char* p = base;
     kw_h8* xp = (kw_h8*)p;
@@ -736,10 +757,10 @@ gl_status knn_wide(const float* x, int64_t n, int32_t d, int32_t k, int32_t* idx
     const int ex = amax > 0.f ? 13 - (int)std::floor(std::log2((double)amax)) : 0;
     const double scale = std::ldexp(1.0, ex);
     if (e == hipSuccess && st == GL_OK) {
-        const int64_t items = (int64_t)plan.nblk * 8 * ((2 * ns + 3) / 4);
+        const int64_t items = (int64_t)nblk * 8 * ((2 * ns + 3) / 4);
         hipLaunchKernelGGL(kw_pack_kernel, dim3((unsigned)((items + 3) / 4)), dim3(256), 0, s, x, (const float*)mu, n, d,
-                           (int64_t)plan.nblk * 8, 2 * ns, (float)scale, xp);
-        hipLaunchKernelGGL(kw_start_kernel, dim3((unsigned)plan.nblk), dim3(256), 0, s, (const float*)norm2, n, np,
+                           (int64_t)nblk * 8, 2 * ns, (float)scale, xp);
+        hipLaunchKernelGGL(kw_start_kernel, dim3((unsigned)nblk), dim3(256), 0, s, (const float*)norm2, n, np,
                            -0.5 * scale * scale, cn);
         e = hipGetLastError();
     }
@@ -766,14 +787,13 @@ gl_status knn_wide(const float* x, int64_t n, int32_t d, int32_t k, int32_t* idx
     // the exact f32 distance (d fused multiply-adds) is within d 2^-24 of the real one, relatively
     const float rel_exact = (float)(1.01 * (d + 2) * std::ldexp(1.0, -24));
     const float m2inv = (float)(-2.0 / (scale * scale));
-    if (st == GL_OK && e == hipSuccess) {
+    for (int32_t first = 0; first < nblk && st == GL_OK && e == hipSuccess; first += step) {
+        const KwPlan plan = kw_plan(nblk, first, std::min(step, nblk - first));
         const auto kernel = T == 8 ? kw_tile_kernel<8> : kw_tile_kernel<12>;
         hipLaunchKernelGGL(kernel, dim3(plan.blocks()), dim3(kWThreads), kWLds, s, (const kw_h8*)xp, (const float*)cn, n,
                            ns, plan, cand);
-        e = hipGetLastError();
-    }
-    if (st == GL_OK && e == hipSuccess) {
-        hipLaunchKernelGGL(kw_refine_kernel, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, s, x, n, d, k,
+        const int64_t queries = std::min((int64_t)plan.nq * kWB, n - (int64_t)first * kWB);
+        hipLaunchKernelGGL(kw_refine_kernel, dim3((unsigned)((queries + 3) / 4)), dim3(256), 0, s, x, n, d, k,
                            (const uint2*)cand, plan, T, (const float*)norm2, m2inv, err_a, err_b, err_c, rel_exact,
                            idx_out, d2_out, fails, counters + 2);
         e = hipGetLastError();

@@ -125,3 +125,24 @@ def test_bounded_arguments():
         gl.knn_bounded(x.double(), 3)
     assert gl.knn_bounded(x, 3)[2] == 500  # few points: scanned
     assert gl.knn_bounded(_mixture(1000, 80, 2), 5)[2] <= 50  # wide: rescans of the certificate
+
+
+# wide features: one block of 256 points (every fourth point per segment), several, and a
+# full round of 64 query blocks with a few left over; both list lengths
+@pytest.mark.parametrize("n,d,k", [(300, 65, 5), (700, 80, 13), (5000, 100, 10), (16500, 70, 12), (17500, 96, 20)])
+def test_wide_in_passes(n, d, k):
+    """Where the candidate lists of all queries cannot be had, the query blocks are taken
+    in passes: the same lists, down to one block per pass, and refused below that."""
+    x = _mixture(n, d, n + d)
+    idx, d2, _ = gl.knn_bounded(x, k)
+    np_, dp = (n + 255) // 256 * 256, (d + 31) // 32 * 32
+    fixed = np_ * (2 * dp + 4) + 8 * n + d * (4 + 8 * 256) + 8 * 256  # operands, norms, list of rescans, means, alignment
+    per = 64 * (8 if k <= 12 else 12) * 8  # bytes of lists per query, at most
+    for blocks in (64, 37, 8, 3, 1):
+        bi, bd, _ = gl.knn_bounded(x, k, temp_bytes=fixed + blocks * 256 * per)
+        assert torch.equal(bi, idx) and torch.equal(bd, d2), blocks
+    if n >= 5000:  # about what a call took with 64 candidates of 4 bytes per query
+        bi, bd, _ = gl.knn_bounded(x, k, temp_bytes=n * (2 * dp + 300))
+        assert torch.equal(bi, idx) and torch.equal(bd, d2)
+    with pytest.raises(gl.GLError, match="memory"):
+        gl.knn_bounded(x, k, temp_bytes=2 * np_ * dp)
