@@ -341,20 +341,53 @@ gl_status kdone(hipError_t e) {
 
 size_t al(size_t b) { return (b + 255) & ~(size_t)255; }
 
-// The graph row by row.  *taken = false, with nothing written, when the rows are
-// not of the kind this is made for: one is longer than kRun (a hub of 262 143
+// Defects of the lists, the rows' lengths (len) and the rows of more than 64 entries
+// (long_rows), found before anything is allocated: the two arrays and the four words
+// behind them lie in the caller's weight array, which has room for 16 n k bytes.
+// The graph is made row by row unless one is longer than kRun (a hub of 262 143
 // entries sorted by one workgroup: 11 ms, the sort of all keys 1.1), or more than
-// one in 16 has over 64 entries.  Finding that out costs such a graph about 0.2 ms.
-gl_status by_rows(int64_t n, int32_t k, const int32_t* idx, const float* d2, int32_t scale_rank, int64_t* row_ptr,
-                  int32_t* col, double* weight, int64_t& count, hipStream_t s, bool* taken) {
+// one in 16 has over 64 entries.
+struct RowShape {
+    int32_t *len, *long_rows;
+    int32_t longest, n_long;
+    bool rows_fit(int64_t n) const { return longest <= kRun && (int64_t)n_long * 16 <= n; }
+};
+
+gl_status row_shape(int64_t n, int32_t k, const int32_t* idx, const float* d2, double* weight, RowShape& r,
+                    hipStream_t s) {
+    const int64_t m = n * k;
+    r.len = (int32_t*)weight;
+    r.long_rows = r.len + n;
+    int32_t* words = r.long_rows + n;  // defects, longest row, long rows
+    const unsigned g_n = (unsigned)((n + 255) / 256);
+    int32_t host[3] = {0, 0, 0};
+    hipError_t e = hipMemsetAsync(words, 0, sizeof(host), s);
+    if (e == hipSuccess) {
+        hipLaunchKernelGGL(kg_init_kernel, dim3(g_n), dim3(256), 0, s, n, k, r.len);
+        hipLaunchKernelGGL(kg_count_kernel, dim3((unsigned)((m + kCountTile - 1) / kCountTile)), dim3(256), 0, s, n, k,
+                           idx, d2, r.len, words);
+        hipLaunchKernelGGL(kg_shape_kernel, dim3(g_n), dim3(256), 0, s, n, (const int32_t*)r.len, r.long_rows,
+                           words + 1);
+        e = hipGetLastError();
+    }
+    if (e == hipSuccess) e = hipMemcpyAsync(host, words, sizeof(host), hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    if (e != hipSuccess) return kdone(e);
+    r.longest = host[1];
+    r.n_long = host[2];
+    return host[0] ? kdefect(host[0]) : GL_OK;
+}
+
+// The graph row by row.
+gl_status by_rows(int64_t n, int32_t k, const int32_t* idx, const float* d2, int32_t scale_rank, const RowShape& shape,
+                  int64_t* row_ptr, int32_t* col, double* weight, int64_t& count, hipStream_t s) {
     const int64_t m = n * k, m2 = 2 * m;
-    *taken = true;
     size_t scan_bytes = 0;
     hipError_t e = hipcub::DeviceScan::ExclusiveSum(nullptr, scan_bytes, (const int32_t*)nullptr, (int32_t*)nullptr,
                                                     (int)n, s);
     if (e != hipSuccess) return kfail(GL_E_HIP, std::string("temporary size query: ") + hipGetErrorString(e));
     const size_t b_keys = al((size_t)m2 * 8), b_w = al((size_t)m2 * 8), b_n = al((size_t)n * 4);
-    const size_t total = b_keys + b_w + 5 * b_n + 256 + al(scan_bytes);
+    const size_t total = b_keys + b_w + 3 * b_n + 256 + al(scan_bytes);
     char* base = nullptr;
     if (hipMallocAsync((void**)&base, total, s) != hipSuccess) {
         (void)hipGetLastError();
@@ -364,62 +397,47 @@ gl_status by_rows(int64_t n, int32_t k, const int32_t* idx, const float* d2, int
     auto take = [&](size_t b) { char* r = q; q += b; return r; };
     unsigned long long* keys = (unsigned long long*)take(b_keys);
     double* wts = (double*)take(b_w);
-    int32_t* len = (int32_t*)take(b_n);
     int32_t* off = (int32_t*)take(b_n);
     int32_t* kept = (int32_t*)take(b_n);
     int32_t* place = (int32_t*)take(b_n);
-    int32_t* long_rows = (int32_t*)take(b_n);
-    int32_t* flags = (int32_t*)take(256);  // defects, longest row, long rows, entries
+    int32_t* flags = (int32_t*)take(256);  // defects, entries
     void* scan_tmp = take(al(scan_bytes));
 
-    const unsigned g_m = (unsigned)((m + 255) / 256), g_n = (unsigned)((n + 255) / 256);
-    int32_t host[4] = {0, 0, 0, 0};
+    const unsigned g_m = (unsigned)((m + 255) / 256);
+    int32_t host[2] = {0, 0};
     gl_status st = GL_OK;
     e = hipMemsetAsync(flags, 0, sizeof(host), s);
+    if (e == hipSuccess) e = hipcub::DeviceScan::ExclusiveSum(scan_tmp, scan_bytes, shape.len, off, (int)n, s);
     if (e == hipSuccess) {
-        hipLaunchKernelGGL(kg_init_kernel, dim3(g_n), dim3(256), 0, s, n, k, len);
-        hipLaunchKernelGGL(kg_count_kernel, dim3((unsigned)((m + kCountTile - 1) / kCountTile)), dim3(256), 0, s, n, k, idx, d2, len, flags);
-        hipLaunchKernelGGL(kg_shape_kernel, dim3(g_n), dim3(256), 0, s, n, (const int32_t*)len, long_rows, flags + 1);
+        hipLaunchKernelGGL(kg_deal_kernel, dim3(g_m), dim3(256), 0, s, n, k, idx, (const int32_t*)off, shape.len, keys);
+        hipLaunchKernelGGL(kg_row_kernel, dim3((unsigned)std::min<int64_t>((n + 3) / 4, kMaxGrid)), dim3(256), 0, s, n,
+                           k, scale_rank, m2, (const int32_t*)off, d2, keys, wts, kept, flags);
+        if (shape.n_long > 0)
+            hipLaunchKernelGGL(kg_long_kernel, dim3((unsigned)std::min(shape.n_long, 512)), dim3(kLongBlock), 0, s, n,
+                               k, scale_rank, m2, (const int32_t*)off, d2, keys, wts, kept,
+                               (const int32_t*)shape.long_rows, shape.n_long, flags);
+        e = hipGetLastError();
+    }
+    if (e == hipSuccess) e = hipcub::DeviceScan::ExclusiveSum(scan_tmp, scan_bytes, kept, place, (int)n, s);
+    if (e == hipSuccess) {  // overwrites shape's arrays
+        hipLaunchKernelGGL(kg_write_kernel, dim3((unsigned)std::min<int64_t>((n + 15) / 16, kMaxGrid)), dim3(256), 0, s,
+                           n, (const int32_t*)off, (const int32_t*)kept, (const int32_t*)place,
+                           (const unsigned long long*)keys, (const double*)wts, row_ptr, col, weight, flags + 1);
         e = hipGetLastError();
     }
     if (e == hipSuccess) e = hipMemcpyAsync(host, flags, sizeof(host), hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e == hipSuccess && host[0]) st = kdefect(host[0]);
-    const int32_t n_long = host[2];
-    if (e == hipSuccess && st == GL_OK && (host[1] > kRun || (int64_t)n_long * 16 > n)) *taken = false;
-    if (e == hipSuccess && st == GL_OK && *taken) {
-        e = hipcub::DeviceScan::ExclusiveSum(scan_tmp, scan_bytes, len, off, (int)n, s);
-        if (e == hipSuccess) {
-            hipLaunchKernelGGL(kg_deal_kernel, dim3(g_m), dim3(256), 0, s, n, k, idx, (const int32_t*)off, len, keys);
-            hipLaunchKernelGGL(kg_row_kernel, dim3((unsigned)std::min<int64_t>((n + 3) / 4, kMaxGrid)), dim3(256), 0,
-                               s, n, k, scale_rank, m2, (const int32_t*)off, d2, keys, wts, kept, flags);
-            if (n_long > 0)
-                hipLaunchKernelGGL(kg_long_kernel, dim3((unsigned)std::min(n_long, 512)), dim3(kLongBlock), 0, s, n, k,
-                                   scale_rank, m2, (const int32_t*)off, d2, keys, wts, kept,
-                                   (const int32_t*)long_rows, n_long, flags);
-            e = hipGetLastError();
-        }
-        if (e == hipSuccess) e = hipcub::DeviceScan::ExclusiveSum(scan_tmp, scan_bytes, kept, place, (int)n, s);
-        if (e == hipSuccess) {
-            hipLaunchKernelGGL(kg_write_kernel, dim3((unsigned)std::min<int64_t>((n + 15) / 16, kMaxGrid)), dim3(256),
-                               0, s, n, (const int32_t*)off, (const int32_t*)kept, (const int32_t*)place,
-                               (const unsigned long long*)keys, (const double*)wts, row_ptr, col, weight, flags + 3);
-            e = hipGetLastError();
-        }
-        if (e == hipSuccess) e = hipMemcpyAsync(host, flags, sizeof(host), hipMemcpyDeviceToHost, s);
-        if (e == hipSuccess) e = hipStreamSynchronize(s);
-        if (e == hipSuccess && host[0]) st = kdefect(host[0]);
-        count = host[3];
-    }
+    count = host[1];
     const hipError_t ef = hipFreeAsync(base, s);
     const hipError_t es = hipStreamSynchronize(s);
     if (st != GL_OK) return st;
     return kdone(e != hipSuccess ? e : (ef != hipSuccess ? ef : es));
 }
 
-// The graph from one sort of all (row, column) keys.
-gl_status by_sort(int64_t n, int32_t k, const int32_t* idx, const float* d2, int32_t scale_rank, int64_t* row_ptr,
-                  int32_t* col, double* weight, int64_t& count, hipStream_t s) {
+// The graph from one sort of all (row, column) keys; checked: the lists have no defects.
+gl_status by_sort(int64_t n, int32_t k, const int32_t* idx, const float* d2, int32_t scale_rank, bool checked,
+                  int64_t* row_ptr, int32_t* col, double* weight, int64_t& count, hipStream_t s) {
     const int64_t m = n * k, m2 = 2 * m;
     // temporaries: keys (2 buffers), values (2), keep, positions, weights, rows, flags, sort storage
     int nbits = 32;
@@ -464,8 +482,10 @@ gl_status by_sort(int64_t n, int32_t k, const int32_t* idx, const float* d2, int
         hipLaunchKernelGGL(kg_emit_kernel, dim3(g_m), dim3(256), 0, s, n, k, idx, d2, k0, v0, flags);
         e = hipGetLastError();
     }
-    if (e == hipSuccess) e = hipMemcpyAsync(&hflags, flags, 4, hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    if (e == hipSuccess && !checked) {
+        e = hipMemcpyAsync(&hflags, flags, 4, hipMemcpyDeviceToHost, s);
+        if (e == hipSuccess) e = hipStreamSynchronize(s);
+    }
     gl_status st = GL_OK;
     if (e == hipSuccess && hflags) st = kdefect(hflags);
     if (e == hipSuccess && st == GL_OK) {
@@ -519,10 +539,16 @@ extern "C" gl_status gl_knn_graph(int64_t n, int32_t k, const int32_t* idx, cons
     hipStream_t s = (hipStream_t)stream;
     if (m2 > (int64_t)INT32_MAX) return kfail(GL_E_INVALID_ARG, "2 n k must be < 2^31");
     int64_t count = 0;
-    bool taken = false;
     gl_status st = GL_OK;
-    if (k <= kRowsK) st = by_rows(n, k, idx, d2, scale_rank, row_ptr, col, weight, count, s, &taken);
-    if (st == GL_OK && !taken) st = by_sort(n, k, idx, d2, scale_rank, row_ptr, col, weight, count, s);
+    RowShape shape = {};
+    const bool checked = k <= kRowsK;
+    if (checked) st = row_shape(n, k, idx, d2, weight, shape, s);
+    if (st == GL_OK) {
+        if (checked && shape.rows_fit(n))
+            st = by_rows(n, k, idx, d2, scale_rank, shape, row_ptr, col, weight, count, s);
+        else
+            st = by_sort(n, k, idx, d2, scale_rank, checked, row_ptr, col, weight, count, s);
+    }
     if (st == GL_OK) *nnz = count;
     return st;
 }
