@@ -8,6 +8,7 @@ import torch
 
 import paper_2303_14495_amd as gl
 from tests.gpu_helpers import DEV, say
+from tests.test_gpu_eigen_sizes import _star_of_cliques
 
 pytestmark = pytest.mark.gpu
 
@@ -81,3 +82,24 @@ def test_complete_graph_ends_at_once(laplacian, n, krylov):
     say(f"K_{n} {laplacian}: lambda {lam:.8e}, residual {res:.1e}, {rs} restarts")
     # residual: rounding of L v, some 2^-24 of its unit rows of n terms of at most 1 (largest magnitudes first)
     assert abs(lam - want) <= 1e-5 * want and res <= 1e-5 * want
+
+
+# 8192 row tiles of 1024 rows and one more: the tiles' norms are added up by every
+# workgroup, or by a launch of their own
+@pytest.mark.parametrize("groups", [1048576, 1048580])
+def test_many_row_tiles(groups):
+    rp, col, w = _star_of_cliques(groups, 8)
+    n = groups * 8
+    op = gl.Operator(rp, col, w, store_w="f32")
+    g = torch.Generator(device=DEV)
+    g.manual_seed(groups)
+    lam, v, res, _ = op.second_eigenpair(torch.randn(n, generator=g, device=DEV), krylov=6, max_restarts=1, tol=1e-9)
+    d = (rp[1:] - rp[:-1]).double()
+    row = torch.repeat_interleave(torch.arange(n, device=DEV), rp[1:] - rp[:-1])
+    x = v.double()
+    y = x - torch.zeros_like(x).index_add_(0, row, x[col.long()] / (d[row] * d[col.long()]).sqrt())
+    say(f"cliques n={n}: lambda {lam:.6e}, residual {res:.3e}")
+    # f32 vectors and products: 2^-24 per entry of unit vectors, a few of them
+    assert abs(float(x.norm()) - 1) <= 1e-6
+    assert abs(float(x @ y) - lam) <= 2e-6
+    assert abs(float((y - lam * x).norm()) - res) <= 2e-6
