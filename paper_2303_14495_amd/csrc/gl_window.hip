@@ -7,6 +7,7 @@
 #include <string>
 #include <vector>
 
+#include "gl_fold.hpp"
 #include "gl_internal.hpp"
 #include "gl_window.hpp"
 
@@ -119,8 +120,10 @@ __global__ __launch_bounds__(64 * kDegWaves) void window_degree_kernel(const flo
     typedef WinPatch<RP, kDegRows> P;
     __shared__ double part[kDegWaves][kDegRows][64];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    const int strips = (w + P::OUT - 1) / P::OUT, by = (int)(blockIdx.x / strips);
-    const int X0 = ((int)blockIdx.x - by * strips) * P::OUT, Y0 = by * kDegRows;
+    const int strips = (w + P::OUT - 1) / P::OUT;
+    const int64_t block = folded(blockIdx.x, blockIdx.y, gridDim.x);
+    if (block >= (int64_t)strips * ((h + kDegRows - 1) / kDegRows)) return;
+    const int by = (int)(block / strips), X0 = (int)(block - (int64_t)by * strips) * P::OUT, Y0 = by * kDegRows;
     const int64_t Jw = (int64_t)w + 2 * RP, Jh = (int64_t)h + 2 * RP;
     const int x = X0 + lane - RP;
     const bool col = lane >= RP && lane < 64 - RP && x < w;
@@ -178,7 +181,9 @@ __global__ __launch_bounds__(256) void window_fill_kernel(const float4* __restri
     const int g = (int)blockIdx.y * 4 + wave;
     if (g >= ng) return;
     const int strips = (tiles_x * kWinTX + P::OUT - 1) / P::OUT;
-    const int ty = (int)(blockIdx.x / strips), X0 = ((int)blockIdx.x - ty * strips) * P::OUT, Y0 = ty * kWinTY;
+    const int64_t block = folded(blockIdx.x, blockIdx.z, gridDim.x);
+    if (block >= (int64_t)strips * ((h + kWinTY - 1) / kWinTY)) return;
+    const int ty = (int)(block / strips), X0 = (int)(block - (int64_t)ty * strips) * P::OUT, Y0 = ty * kWinTY;
     const int64_t Jw = (int64_t)w + 2 * RP, Jh = (int64_t)h + 2 * RP;
     const int x = X0 + lane - RP;
     const bool col = x < w;
@@ -276,8 +281,8 @@ template <int RP>
 hipError_t launch_degree_t(const WinBuild& b, const gl_operator* op, double* root, int32_t* flags,
                            unsigned long long* first_bad, hipStream_t s) {
     constexpr int out = WinPatch<RP, kDegRows>::OUT;
-    const dim3 grid((unsigned)((op->wwidth + out - 1) / out * ((op->wheight + kDegRows - 1) / kDegRows)));
-    hipLaunchKernelGGL(window_degree_kernel<RP>, grid, dim3(64 * kDegWaves), 0, s, b.J, op->wheight, op->wwidth, op->wr,
+    const Fold f = fold_blocks((int64_t)((op->wwidth + out - 1) / out) * ((op->wheight + kDegRows - 1) / kDegRows));
+    hipLaunchKernelGGL(window_degree_kernel<RP>, dim3(f.x, f.y), dim3(64 * kDegWaves), 0, s, b.J, op->wheight, op->wwidth, op->wr,
                        b.c4, b.al, b.inv_s2, op->degree, root, flags, first_bad);
     return hipGetLastError();
 }
@@ -287,7 +292,9 @@ hipError_t launch_fill_t(const WinBuild& b, const gl_operator* op, int raw_mode,
     constexpr int GS = 16 / (int)sizeof(TW), out = WinPatch<RP, kWinTY>::OUT;
     const int tiles_y = (op->wheight + kWinTY - 1) / kWinTY;
     const int strips = (op->wtiles_x * kWinTX + out - 1) / out;
-    const dim3 grid((unsigned)(strips * tiles_y), (unsigned)((window_groups(op->wM, GS) + 3) / 4));
+    // a narrow image of 2^25 rows has two strips of 2^23 workgroups: 2^32 threads
+    const Fold f = fold_blocks((int64_t)strips * tiles_y);
+    const dim3 grid(f.x, (unsigned)((window_groups(op->wM, GS) + 3) / 4), f.y);
     hipLaunchKernelGGL((window_fill_kernel<RP, TW>), grid, dim3(256), 0, s, b.J, b.root, op->wheight, op->wwidth, op->wr,
                        op->wtiles_x, op->wM, b.c4, b.al, b.inv_s2, raw_mode, (u32x4*)op->w);
     return hipGetLastError();

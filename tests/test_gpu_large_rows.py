@@ -55,3 +55,25 @@ def test_knn_folded(n, d, span):
         assert torch.equal(idx[q].to(torch.int64), best % n), q
         assert torch.equal(d2[q].to(torch.int64), best // n), q
     say(f"knn n={n} d={d}: {len(rows)} rows")
+
+
+def test_window_of_a_tall_image():
+    """One column of 2^25 + 5 pixels of one colour: its two strips are 2^32 threads when the
+    weights are stored.  Every weight is 1, degrees 1 at the ends and 2 inside."""
+    if torch.cuda.mem_get_info()[0] < 100e9:
+        pytest.skip("needs 100 GB of device memory")
+    n = 2**25 + 5
+    op = gl.Operator.window(torch.full((n, 1, 1), 0.5, device=DEV), window_radius=1, patch_radius=1, sigma=1.0, store_w="f32")
+    x = (torch.arange(n, device=DEV) % 509).to(torch.float32).unsqueeze(1)
+    y = op.laplacian_apply(x)[:, 0]
+    r = torch.full((n,), 2.0, device=DEV)
+    r[0] = r[-1] = 1.0
+    v = x[:, 0]
+    edge = 1.0 / (r[1:] * r[:-1]).sqrt()
+    want = v.clone()
+    want[1:] -= edge * v[:-1]
+    want[:-1] -= edge * v[1:]
+    worst = float((y - want).abs().max())
+    say(f"window of {n} x 1: max error {worst:.1e}")
+    assert worst <= 4 * 509 * 2.0**-23  # two products of values below 509 and weights of at most 1
+    op.close()
