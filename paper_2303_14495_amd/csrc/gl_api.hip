@@ -978,8 +978,8 @@ gl_status gl_power_max_eig(const gl_operator* op, int32_t iters, const float* x0
         }
         return hipGetLastError();
     };
-    auto finalize = [&](int scale_stat) -> hipError_t {
-        hipLaunchKernelGGL(gl::power_finalize_kernel, dim3(1), dim3(256), 0, s, partials, r.grid, scale_stat,
+    auto finalize = [&](int scale_stat, bool first) -> hipError_t {
+        hipLaunchKernelGGL(gl::power_finalize_kernel, dim3(1), dim3(256), 0, s, partials, r.grid, scale_stat, first ? 1 : 0,
                            scale, sums);
         return hipGetLastError();
     };
@@ -989,63 +989,64 @@ gl_status gl_power_max_eig(const gl_operator* op, int32_t iters, const float* x0
         GL_HIP(permute_rows(op, 4, x0, xp, false, s), "power permute");
         x0 = xp;
     }
-    double h[2] = {0, 0};
+    double h[3] = {0, 0, 0};  // the two sums, and whether a norm was lost
     auto read_sums = [&]() -> hipError_t {
         const hipError_t e = hipMemcpyAsync(h, sums, sizeof(h), hipMemcpyDeviceToHost, s);
         return e == hipSuccess ? hipStreamSynchronize(s) : e;
     };
-    // s_0 = 1/|x0| from the mode-1 pass over x0
-    GL_HIP(pass(x0, nullptr, 1, 1.0f, nullptr), "power launch");
-    GL_HIP(finalize(1), "power finalize");
-    // The norm only keeps the iterates within float's range, so it is divided out
-    // every few products: the others need neither the sums nor the launch that adds
-    // them up (4 of 17 us per product on a 453 x 601 image).  How few: |L x| / |x|
-    // never falls from one iterate to the next (L is symmetric, without negative
-    // eigenvalues) and is at most 2 dmax, so the first product's ratio bounds all
-    // later ones.  With a gain, a power of two, in the middle of those bounds an
-    // iterate stays within 2^+-40 of 1, whose squares float can add up.  16 products,
-    // with the gain at the upper end, where the bounds are close (a start vector
-    // that is spread over the spectrum); every product where they are far apart.
-    float gain = (float)std::ldexp(1.0, std::min(126, -(int)std::ceil(std::log2(2.0 * op->dmax))));  // about 1 / (2 dmax)
+    // The norm only keeps the iterates within float's range.  With a gain, a power of
+    // two of about 1 / (2 dmax), a product changes it by a factor between 1/4 and 1
+    // once the largest eigenvectors lead (the largest eigenvalue is at least dmax),
+    // so it is divided out every 16 products: the others need neither the sums nor
+    // the launch that adds them up (4 of 17 us per product on a 453 x 601 image).
+    float gain = (float)std::ldexp(1.0, std::min(126, -(int)std::ceil(std::log2(2.0 * op->dmax))));
     int every = 16;
     const float* x = x0;
-    const float* sc = scale;
-    for (int it = 0, run = 0; it < iters; ++it) {
-        float* y = buf[it & 1];
-        const bool norm = it + 1 < iters && (it == 0 || ++run == every);  // of y, for the next product
-        GL_HIP(pass(x, y, norm ? 0 : 2, gain, sc), "power launch");
-        if (norm) GL_HIP(finalize(0), "power finalize");
-        sc = norm ? scale : nullptr;
-        if (norm) run = 0;
-        if (it == 0 && norm) {
-            // |L x| / |x| of the first product against 2 dmax
-            GL_HIP(read_sums(), "power method");
-            if (!(h[0] > 0x1p-90)) {  // the squares' sum is lost, or nearly: the product as it is
-                gain = 1.0f;
-                GL_HIP(pass(x, nullptr, 1, 1.0f, nullptr), "power launch");
-                GL_HIP(finalize(1), "power finalize");
-                GL_HIP(pass(x, y, 0, gain, scale), "power launch");
-                GL_HIP(finalize(0), "power finalize");
-                GL_HIP(read_sums(), "power method");
-            }
-            const double ratio = std::log2(std::sqrt(h[0]) / gain), top = std::log2(2.0 * op->dmax);
-            const double spread = top - ratio;
-            if (!(spread <= 80.0)) {  // also where the ratio is 0 or not a number
-                gain = 1.0f;
-                every = 1;
-            } else if (spread > 1.5) {
-                gain = (float)std::ldexp(1.0, (int)std::lrint(std::fmax(-126.0, std::fmin(126.0, -0.5 * (ratio + top)))));
-                every = std::max(1, std::min(16, (int)(80.0 / (spread + 1.0))));
-            } else {  // no hurry: the first norm is not used
-                sc = nullptr;
-                run = 1;
-            }
+    auto products = [&](int it, const float* sc) -> hipError_t {  // from product `it` on; sc: of its argument
+        for (int run = 0; it < iters; ++it) {
+            float* y = buf[it & 1];
+            const bool norm = ++run == every && it + 1 < iters;  // of y, for the next product
+            hipError_t e = pass(x, y, norm ? 0 : 2, gain, sc);
+            if (e == hipSuccess && norm) e = finalize(0, false);
+            if (e != hipSuccess) return e;
+            if (norm) run = 0;
+            sc = norm ? scale : nullptr;
+            x = y;
         }
-        x = y;
+        hipError_t e = pass(x, nullptr, 1, 1.0f, nullptr);
+        if (e == hipSuccess) e = finalize(1, false);
+        return e == hipSuccess ? read_sums() : e;
+    };
+    // s_0 = 1/|x0| from the mode-1 pass over x0
+    GL_HIP(pass(x0, nullptr, 1, 1.0f, nullptr), "power launch");
+    GL_HIP(finalize(1, true), "power finalize");
+    GL_HIP(products(0, scale), "power method");
+    if (h[2] != 0.0 && iters > 0) {
+        // A squared norm below 2^-90, whose terms float may not hold: a start vector
+        // without weight on the upper spectrum.  Again, with bounds: |L x| / |x| never
+        // falls from one iterate to the next (L is symmetric, without negative
+        // eigenvalues) and is at most 2 dmax, so the first product's ratio bounds all
+        // later ones, and with a gain in the middle of those bounds, and a norm often
+        // enough, every iterate stays within 2^+-40 of 1.
+        const double top = std::log2(2.0 * op->dmax);
+        for (;; gain = 1.0f) {
+            GL_HIP(pass(x0, nullptr, 1, 1.0f, nullptr), "power launch");
+            GL_HIP(finalize(1, true), "power finalize");
+            GL_HIP(pass(x0, buf[0], 0, gain, scale), "power launch");
+            GL_HIP(finalize(0, false), "power finalize");
+            GL_HIP(read_sums(), "power method");
+            if (h[0] > 0x1p-90 || gain == 1.0f) break;  // else the product as it is
+        }
+        const double ratio = std::log2(std::sqrt(h[0]) / gain), spread = top - ratio;
+        gain = 1.0f;
+        every = 1;  // also where the ratio is 0 or not a number
+        if (spread <= 80.0) {
+            gain = (float)std::ldexp(1.0, (int)std::lrint(std::fmax(-126.0, std::fmin(126.0, -0.5 * (ratio + top)))));
+            every = std::max(1, std::min(16, (int)(80.0 / (spread + 1.0))));
+        }
+        x = buf[0];
+        GL_HIP(products(1, scale), "power method");
     }
-    GL_HIP(pass(x, nullptr, 1, 1.0f, nullptr), "power launch");
-    GL_HIP(finalize(1), "power finalize");
-    GL_HIP(read_sums(), "power method");
     if (!(h[1] > 0) || !std::isfinite(h[0]) || !std::isfinite(h[1]))
         return fail(GL_E_NONFINITE, "power method: x0 is zero or the iteration is not finite");
     *rayleigh = h[0] / h[1];

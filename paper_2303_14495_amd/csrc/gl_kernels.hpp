@@ -86,20 +86,22 @@ __global__ __launch_bounds__(kBlock) void finalize_group_kernel(const P* partial
     }
 }
 
-// Power method: scale_out = 1 / sqrt(sum partial[scale_stat]); sums_out (optional)
-// gets both sums in double.
+// Power method: scale_out = 1 / sqrt(sum partial[scale_stat]); sums_out gets both
+// sums in double, and sums_out[2] 0 with `first`, 1 once the one of scale_stat is
+// below 2^-90 or no number.
 static __global__ __launch_bounds__(kBlock) void power_finalize_kernel(const float* partials, int64_t nb,
-                                                                int32_t scale_stat, float* scale_out,
+                                                                int32_t scale_stat, int32_t first, float* scale_out,
                                                                 double* sums_out) {
     const double s0 = block_sum(partials, nb);
     __syncthreads();
     const double s1 = block_sum(partials + nb, nb);
     if (threadIdx.x == 0) {
-        if (scale_out) *scale_out = (float)(1.0 / sqrt(scale_stat ? s1 : s0));
-        if (sums_out) {
-            sums_out[0] = s0;
-            sums_out[1] = s1;
-        }
+        const double norm2 = scale_stat ? s1 : s0;
+        *scale_out = (float)(1.0 / sqrt(norm2));
+        sums_out[0] = s0;
+        sums_out[1] = s1;
+        if (first) sums_out[2] = 0.0;
+        else if (!(norm2 >= 0x1p-90)) sums_out[2] = 1.0;
     }
 }
 
