@@ -216,8 +216,11 @@ typedef struct gl_window_graph {
 } gl_window_graph;
 
 /* Build the operator of a window graph on the device, with implicit columns
- * (layout GL_LAYOUT_WINDOW): the weights are computed in F64 once, the degrees
- * d_i summed in F64 in increasing neighbour order, and the stored weights
+ * (layout GL_LAYOUT_WINDOW): the weights are computed in F64, with the same bits
+ * from both ends of a pair and each time they are needed (for the degrees and
+ * for storing them); a degree d_i is summed in F64, the window rows v, v + 8, ..
+ * counted from its first, offsets in order, for v = 0 .. 7, then the eight sums
+ * in order; and the stored weights
  * (what_ij for L_s, w_ij for L, rounded to `store_w`) kept once per pair: each
  * pixel keeps the first half of its window in scan order (dy < 0, or dy = 0
  * and dx < 0), and W being symmetric, the other half is its neighbours';
@@ -229,8 +232,8 @@ typedef struct gl_window_graph {
  * and gl_laplacian_apply takes that buffer from the stream-ordered allocator
  * for the call.  One call with K columns needs
  * 2 K * (64 + 2r) * (4 + r) * (4 or 8 bytes) <= 147456 of LDS, checked per
- * call (GL_E_INVALID_ARG).  Construction holds 8 bytes per pixel and window
- * offset of temporary device memory.  Synchronises `stream`.  Errors: GL_E_INVALID_ARG,
+ * call (GL_E_INVALID_ARG).  Construction holds about 24 bytes per pixel of
+ * temporary device memory.  Synchronises `stream`.  Errors: GL_E_INVALID_ARG,
  * GL_E_BAD_GRAPH (a pixel whose weights all underflow to zero: a degree of
  * 0), GL_E_DTYPE, GL_E_NOMEM, GL_E_HIP. */
 gl_status gl_window_operator_create(const gl_window_graph *graph, gl_dtype store_w, void *stream,
@@ -264,7 +267,10 @@ gl_status gl_power_workspace_size(const gl_operator *op, size_t *bytes);
 
 /* Power method for the largest eigenvalue of the operator's Laplacian
  * (Section 3.1; Section 5.1.1 uses 150 iterations): x <- x0/|x0|, then
- * `iters` times x <- L x / |L x|, in F32 with F64 norms.  Host outputs:
+ * `iters` times x <- L x / |L x|, in F32 with F64 norms (the norm divided out
+ * every 16 products; where an x so formed leaves float's range, the call begins
+ * again and divides as often as the ratio |L x| / |x| of the first product
+ * asks for).  Host outputs:
  * *rayleigh = x^T L x of the final unit vector (L_s or L, as the operator's),
  * *lambda_hat = min(2 dmax, 1.01 * rayleigh) with dmax = 1 for L_s and the
  * largest stored diagonal for L, an upper estimate kept feasible by
@@ -290,10 +296,13 @@ gl_status gl_power_max_eig(const gl_operator *op, int32_t iters, const float *x0
  *             row, no self-loops): a gl_graph ready for gl_operator_create
  *   capacity  >= 2 n k;  *nnz (host out)
  * 2 <= n < 2^31, 1 <= k <= min(n-1, 1024), 2 n k < 2^31, 1 <= scale_rank <= k.
- * Allocates about 32 n k bytes of stream-ordered temporaries (80 n k when k > 24 or
- * a point is in more than 4096 lists); synchronises `stream`.  Errors: GL_E_INVALID_ARG (also an index out of range or equal
- * to its row, a negative or non-finite distance), GL_E_BAD_GRAPH (a point
- * whose weights are all 0), GL_E_NOMEM, GL_E_HIP. */
+ * Allocates about n (32 k + 12) bytes of stream-ordered temporaries; 104 n k and
+ * the sort's own when k > 24, a row (its list and the points that list it) has
+ * more than 4096 entries, or more than one row in 16 has over 64.  `weight` also
+ * serves as scratch, whatever the outcome.  Synchronises `stream`.  Errors:
+ * GL_E_INVALID_ARG (also an index out of range or equal to its row, a negative
+ * or non-finite distance), GL_E_BAD_GRAPH (a point whose weights are all 0),
+ * GL_E_NOMEM, GL_E_HIP. */
 gl_status gl_knn_graph(int64_t n, int32_t k, const int32_t *idx, const float *d2, int32_t scale_rank,
                        int64_t *row_ptr, int32_t *col, double *weight, int64_t capacity, int64_t *nnz,
                        void *stream);
@@ -508,27 +517,31 @@ gl_status gl_server_destroy(gl_server *srv);
  *   d2_out   device f32 [n x k] or NULL: those squared distances, computed
  *            as sum_c (x_ic - x_jc)^2 in f32 in coordinate order
  * 1 <= d <= 4096, 1 <= k <= 32, k < n < 2^31.
- * d <= 64: asynchronous on `stream`; a
- * point with a non-finite coordinate is never chosen as a neighbour, and a
- * list that cannot be filled ends with index -1 and distance +inf.  Few points,
- * d = 1, a stream under capture and a failed allocation: one scan per query,
- * no temporary memory.  Otherwise approximate distances from the matrix
- * cores (points split into two f16 parts, f32 accumulation), exact f32
- * distances of each query's candidates, a proof from the rounding bounds that
- * no other point can enter or tie, and the scan for queries without it; about
- * n (40 d + 200) to n (40 d + 1600) bytes of stream-ordered temporaries (the
- * more the fewer the points).
+ * d <= 64: asynchronous on `stream`; a point with a non-finite coordinate is
+ * never chosen as a neighbour, and a list that cannot be filled ends with index
+ * -1 and distance +inf.  Few points, d = 1, a stream under capture and a failed
+ * allocation: every query over all points, no temporary memory.  Otherwise
+ * approximate distances from the matrix cores (points split into two f16 parts,
+ * f32 accumulation), exact f32 distances of each query's candidates, a proof
+ * from the rounding bounds that no other point can enter or tie, and all points
+ * for the queries without it (mostly ties at the k-th place).  Stream-ordered
+ * temporaries: n (o + l + 16) bytes, o = 32 to 416 for the operands of the
+ * products (6.5 d to 16 d), l = segments (8 T + 4) for the candidates, T = 8 for
+ * k <= 4 up to 36 for k > 28, and 8 segments up to 8192 points, 4 up to
+ * 16 384, 2 up to 32 768, then 1.
  * d > 64 (wide features, e.g. 784 pixels): the same result, found through
  * the matrix cores: <x_i, x_j> of the centred points rounded to f16 (scaled
  * by a power of two), f32 accumulation, in one fused kernel that filters
  * every block of products into per-query candidate lists without storing
- * them; the candidates of a query that can be among the k best get their
- * exact distances recomputed (64 at most), and a certificate from the rounding-error bound proves that no other point can
- * enter or tie the k best; queries without it are rescanned exactly
- * (gl_knn_fallback_rows).  Non-finite coordinates are rejected
- * (GL_E_INVALID_ARG).  Allocates about n (2 d + 1100) bytes, below
- * 16 384 points up to n (2 d + 6200), as stream-ordered temporaries and
- * synchronises `stream`.
+ * them; the candidates of a query that can be among the k best get their exact
+ * distances recomputed (64 at most), and a certificate from the rounding-error
+ * bound proves that no other point can enter or tie the k best; queries without
+ * it are rescanned exactly (gl_knn_fallback_rows).  Non-finite coordinates are
+ * rejected (GL_E_INVALID_ARG).  Allocates n (2 d + 16) bytes of stream-ordered
+ * temporaries, d rounded up to 32 and n to 256, and candidate lists: 1024 bytes
+ * per query for k <= 12 and 1536 above, up to four times that for the queries
+ * beyond a multiple of 16 384; where these cannot be had, of as few as 256
+ * queries at a time.  Synchronises `stream`.
  * Errors: GL_E_INVALID_ARG, GL_E_NOMEM, GL_E_HIP. */
 gl_status gl_knn(const float *x, int64_t n, int32_t d, int32_t k, int32_t *idx_out,
                  float *d2_out, void *stream);

@@ -7,8 +7,8 @@
 // their rows; a wavefront then sorts its row (about 2k entries) by column, drops
 // second occurrences and zero weights, and the kept ones move to their final
 // places.  Every entry is written three times; the one sort of all (row, column)
-// keys with their values moves each entry seven times and needs 80 bytes of
-// temporaries per list entry against 32.  What bounds it now is mapping those and
+// keys with their values moves each entry seven times and needs 104 bytes of
+// temporaries per list entry, and the sort's own, against 32.  What bounds it now is mapping those and
 // the two host round trips.  Whole calls on lists of 10: 20 000 points 395 us
 // sorted and 218 by rows, 100 000: 835 and 289, 262 144: 1097 and 668.
 #include <hip/hip_runtime.h>

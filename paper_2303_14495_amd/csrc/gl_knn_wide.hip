@@ -241,8 +241,10 @@ int64_t kw_lists(int32_t nblk, int32_t step) {
 // LDS; queues are emptied into the lists (T med3 steps each) when one may
 // overflow, after eight points, and at the end of the lane's 64.
 // 70 000 x 784, k = 10: 8.4 ms (910 TFLOP/s) against 17.7 with 32 x 64 products per
-// wavefront and distances exchanged through LDS, of which about 2.5 are selection;
-// the whole call 21.5 -> 10.4 ms, with k = 32 78 -> 10.9.
+// wavefront and distances exchanged through LDS; 25, 12, 6 and 3 staging steps (784, 384,
+// 192 and 96 coordinates) take 8.65, 5.01, 3.58 and 2.95, which is 0.28 per step and
+// 1.6 for selection and the blocks' starts at the long end.  The whole call 21.5 ->
+// 10.4 ms, with k = 32 78 -> 10.9.
 template <int T>
 __global__ __launch_bounds__(kWThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void kw_tile_kernel(
     const kw_h8* __restrict__ xp, const float* __restrict__ cn, int64_t n, int32_t ns, KwPlan plan,
