@@ -312,8 +312,9 @@ gl_status gl_knn_graph(int64_t n, int32_t k, const int32_t *idx, const float *d2
  * smallest eigenvalue lambda_2 of the operator's Laplacian (L_s or L) and a
  * unit eigenvector, by Lanczos with full reorthogonalisation on the
  * operator's own product, deflated against the null vector (D^{1/2} 1 for L_s,
- * 1 for L), restarted from the Ritz vector until |L v - lambda_2 v| <= tol or
- * `max_restarts` restarts have run.
+ * 1 for L), restarted from the Ritz vector until |L v - lambda_2 v| <= tol,
+ * `max_restarts` restarts have run, or one has left the vector as it was (its
+ * residual is at the rounding of L v).
  *   krylov        Lanczos steps per restart, 2..512 (capped at n - 1)
  *   x0            device float [n], node order: start vector, not parallel
  *                 to the null vector
