@@ -28,9 +28,12 @@ def _lists(n, k, kind):
     return idx, (0.25 + (lo * 29 + hi * 13) % 101 / 64.0).astype(np.float32)
 
 
-# rows longer than 4096 entries, and more than one in 16 of over 64, go to the sort
+# rows longer than 4096 entries, and more than one in 16 of over 64, go to the sort, as do
+# lists of 25 and more; its keys have as many bits as n - 1, twice: both sides of powers of two
 @pytest.mark.parametrize("n,k,kind", [(2, 1, "any"), (3, 1, "any"), (3, 2, "any"), (5, 4, "any"), (65, 24, "any"), (66, 25, "any"),
-                                      (4095, 2, "hub"), (4300, 3, "hub"), (1300, 10, "few"), (700, 24, "few"), (257, 7, "few")])
+                                      (4095, 2, "hub"), (4300, 3, "hub"), (1300, 10, "few"), (700, 24, "few"), (257, 7, "few"),
+                                      (26, 25, "any"), (32, 25, "any"), (33, 25, "any"), (64, 30, "any"), (65, 30, "any"),
+                                      (128, 100, "any"), (129, 26, "few"), (1024, 30, "any"), (1025, 30, "any")])
 def test_against_the_oracle(n, k, kind):
     idx, d2 = _lists(n, k, kind)
     rp, col, w = (t.cpu().numpy() for t in gl.knn_graph(torch.from_numpy(idx).to(DEV), torch.from_numpy(d2).to(DEV), k))
