@@ -296,7 +296,7 @@ gl_status gl_power_max_eig(const gl_operator *op, int32_t iters, const float *x0
  *             row, no self-loops): a gl_graph ready for gl_operator_create
  *   capacity  >= 2 n k;  *nnz (host out)
  * 2 <= n < 2^31, 1 <= k <= min(n-1, 1024), 2 n k < 2^31, 1 <= scale_rank <= k.
- * Allocates about n (32 k + 12) bytes of stream-ordered temporaries; 104 n k and
+ * Allocates about n (32 k + 12) bytes of stream-ordered temporaries; 88 n k and
  * the sort's own when k > 24, a row (its list and the points that list it) has
  * more than 4096 entries, or more than one row in 16 has over 64.  `weight` also
  * serves as scratch, whatever the outcome.  Synchronises `stream`.  Errors:

@@ -7,8 +7,9 @@
 // their rows; a wavefront then sorts its row (about 2k entries) by column, drops
 // second occurrences and zero weights, and the kept ones move to their final
 // places.  Every entry is written three times; the one sort of all (row, column)
-// keys with their values moves each entry seven times and needs 104 bytes of
-// temporaries per list entry, and the sort's own, against 32.  What bounds it now is mapping those and
+// keys with their values moves each entry once per 8 bits of its key (5 times at
+// 262 144 points) and needs 88 bytes of temporaries per list entry, and the sort's
+// own, against 32.  What bounds it now is mapping those and
 // the two host round trips.  Whole calls on lists of 10: 20 000 points 395 us
 // sorted and 218 by rows, 100 000: 835 and 289, 262 144: 1097 and 668.
 #include <hip/hip_runtime.h>
@@ -25,7 +26,11 @@ namespace {
 constexpr int kLongBlock = 1024;
 constexpr int kRun = 4096;  // keys sorted in LDS (32 KB: two workgroups of 16 waves fill a CU)
 
-constexpr int kCountTile = 1024;
+constexpr int kCountTile = 1024;  // slots of the count's hash, and entries of a workgroup;
+// four times the entries from kCountLong on, where that still fills the chip: a hub's
+// additions are a quarter (262 144 lists of 10 with a hub: 1.24 -> 1.13 ms), and without
+// one the count takes as long (100 us)
+constexpr int64_t kCountLong = 1 << 21;
 // Lists of up to kRowsK go by rows (60 000 points, sorted / by rows: lists of 4 347 /
 // 272 us, 16 776 / 314, 24 863 / 313); beyond, most rows have more than a
 // wavefront's 64 entries and a workgroup each costs more than the sort (lists of
@@ -49,9 +54,9 @@ __global__ __launch_bounds__(256) void kg_init_kernel(int64_t n, int32_t k, int3
 
 // len[j] += 1 for every list that holds j (len starts at k); defects flagged.
 // Additions to one address are served one every 12 ns (3.2 ms for a point in
-// 262 143 lists), so a workgroup first adds up its kCountTile entries in LDS: one
-// slot per hash, the first point that takes it; others add straight to memory.
-__global__ __launch_bounds__(256) void kg_count_kernel(int64_t n, int32_t k, const int32_t* __restrict__ idx,
+// 262 143 lists), so a workgroup first adds up its `span` entries in LDS: one slot
+// per hash, the first point that takes it; others add straight to memory.
+__global__ __launch_bounds__(256) void kg_count_kernel(int64_t n, int32_t k, int32_t span, const int32_t* __restrict__ idx,
                                                        const float* __restrict__ d2, int32_t* __restrict__ len,
                                                        int32_t* flags) {
     __shared__ int32_t owner[kCountTile], times[kCountTile];
@@ -60,7 +65,7 @@ __global__ __launch_bounds__(256) void kg_count_kernel(int64_t n, int32_t k, con
         times[u] = 0;
     }
     __syncthreads();
-    const int64_t t0 = (int64_t)blockIdx.x * kCountTile, t1 = min(t0 + kCountTile, n * k);
+    const int64_t t0 = (int64_t)blockIdx.x * span, t1 = min(t0 + span, n * k);
     for (int64_t t = t0 + threadIdx.x; t < t1; t += 256) {
         const int32_t j = idx[t];
         const bool ok = j >= 0 && j < n && j != t / k;
@@ -366,8 +371,9 @@ gl_status row_shape(int64_t n, int32_t k, const int32_t* idx, const float* d2, d
     hipError_t e = hipMemsetAsync(words, 0, sizeof(host), s);
     if (e == hipSuccess) {
         hipLaunchKernelGGL(kg_init_kernel, dim3(g_n), dim3(256), 0, s, n, k, r.len);
-        hipLaunchKernelGGL(kg_count_kernel, dim3((unsigned)((m + kCountTile - 1) / kCountTile)), dim3(256), 0, s, n, k,
-                           idx, d2, r.len, words);
+        const int32_t span = m < kCountLong ? kCountTile : 4 * kCountTile;
+        hipLaunchKernelGGL(kg_count_kernel, dim3((unsigned)((m + span - 1) / span)), dim3(256), 0, s, n, k, span, idx, d2,
+                           r.len, words);
         hipLaunchKernelGGL(kg_shape_kernel, dim3(g_n), dim3(256), 0, s, n, (const int32_t*)r.len, r.long_rows,
                            words + 1);
         e = hipGetLastError();

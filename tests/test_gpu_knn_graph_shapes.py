@@ -58,3 +58,25 @@ def test_defects_in_either(kind):
             bd[0, 0] = np.nan
         with pytest.raises(gl.GLError):
             gl.knn_graph(torch.from_numpy(bi).to(DEV), torch.from_numpy(bd).to(DEV), 3)
+
+
+# 2^21 list entries and more: four times the entries per workgroup of the count
+@pytest.mark.parametrize("n,k,hub", [(209715, 10, True), (209720, 10, True), (209720, 10, False), (110000, 20, False)])
+def test_large_structure(n, k, hub):
+    """Row offsets and columns of the union of random lists, with a point in all of them or none."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(n + k)
+    i = torch.arange(n, device=DEV)
+    step = torch.randint(1, n // k, (n, k), generator=g, device=DEV) + torch.arange(k, device=DEV) * (n // k)
+    idx = (i[:, None] + step) % n
+    if hub:
+        idx[:, 0] = torch.where((idx[:, 1:] == 7).any(1) | (i == 7), idx[:, 0], 7)
+    d2 = torch.sort(torch.rand(n, k, generator=g, device=DEV), 1).values + 0.1
+    rp, col, w = gl.knn_graph(idx.to(torch.int32), d2, k)
+    a, b = i.repeat_interleave(k), idx.reshape(-1)
+    key = torch.unique(torch.cat([a * n + b, b * n + a]))
+    want = torch.zeros(n + 1, dtype=torch.int64, device=DEV)
+    want[1:] = torch.cumsum(torch.bincount(key // n, minlength=n), 0)
+    say(f"knn graph n={n} k={k}: longest row {int((want[1:] - want[:-1]).max())}")
+    assert torch.equal(rp, want) and torch.equal(col.to(torch.int64), key % n)
+    assert bool((w > 0).all())
