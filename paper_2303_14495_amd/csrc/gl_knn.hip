@@ -626,6 +626,12 @@ __global__ __launch_bounds__(kBlockQ, (KnnBlock<D, KM>::waves)) void knn_block_k
                     acc[u] = fmaf(t, t, acc[u]);
                 }
             }
+            float nearest = acc[0];
+#pragma unroll
+            for (int u = 1; u < P; ++u) nearest = fminf(nearest, acc[u]);
+            // one branch for all of them in most steps (100 000 points, d = 2: 6.3 -> 4.1 ms; not
+            // where it has the compiler hold the points' reads back: d = 64, k = 15 50 -> 57)
+            if ((D <= 40 || KM > 16) && !(nearest < thr)) continue;
 #pragma unroll
             for (int u = 0; u < P; ++u) {
                 const int64_t j = base + p + u;
@@ -702,15 +708,15 @@ void knn_block_launch(const float* x, int64_t n, int32_t d, int32_t k, const Knn
 
 // Queries from which on knn_block_kernel is the faster of the two, whose time does
 // not depend on their number up to some 65 000.  With a k-th distance to start from
-// (100 000 points, k = 15, scan / block in ms without the 1.7 to 7.2 of the products):
-// d = 2: 30 000 queries 3.6 / 5.8, 60 000 7.5 / 6.3; d = 10: 7.6 / 11.1 and 15.4 / 11.4;
-// d = 27: 16 000 11.1 / 21.9, 30 000 23.9 / 21.9; d = 64: 19.8 / 41.9 and 43.1 / 41.9.
-int64_t knn_block_min_listed(int32_t d) { return d <= 3 ? 48000 : d <= 16 ? 40000 : 28000; }
+// (100 000 points, k = 15, scan / block in ms without the 1.6 to 7.1 of the products):
+// d = 2: 30 000 queries 3.6 / 4.0, 60 000 7.5 / 4.0; d = 10: 7.5 / 8.7 and 15.4 / 8.7;
+// d = 27: 16 000 11.1 / 21.1, 30 000 23.9 / 21.1; d = 64: 19.8 / 42.3 and 43.1 / 42.3.
+int64_t knn_block_min_listed(int32_t d) { return d <= 16 ? 36000 : 28000; }
 
-// Without one (every point, k = 15): d = 3: 65 000 points 5.2 / 4.9, k = 32: 100 000
-// 13.4 / 14.1; d = 10: 48 000 4.4 / 5.7, 65 000 8.0 / 7.5; d = 27: 32 000 6.5 / 7.3,
-// 48 000 14.2 / 11.0; d = 64: 13.7 / 15.2 and 28.9 / 21.9.
-int64_t knn_block_min(int32_t d, int32_t k) { return d > 16 ? 36000 : d <= 3 && k > 16 ? 110000 : 60000; }
+// Without one (every point, k = 15): d = 3: 48 000 points 2.9 / 2.7, 65 000 5.2 / 3.6, k = 32:
+// 100 000 13.4 / 14.1; d = 10: 48 000 4.4 / 4.6, 65 000 8.0 / 6.2; d = 27: 32 000 6.5 / 7.3,
+// 48 000 14.2 / 10.5; d = 64: 13.7 / 15.2 and 28.9 / 21.9.
+int64_t knn_block_min(int32_t d, int32_t k) { return d > 16 ? 36000 : d <= 3 && k > 16 ? 110000 : 50000; }
 
 // The queries of r by whichever of the two kernels they are enough for: known here
 // for every point, on the device for a list.

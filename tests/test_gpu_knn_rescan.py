@@ -46,10 +46,11 @@ def _check(x, k, idx, d2, seed):
     assert torch.equal(d2[rows].to(torch.int64), want_d)
 
 
-# listed queries: the limits are 48 000 (d <= 3), 40 000 (d <= 16) and 28 000; k at the
+# listed queries: the limits are 36 000 (d <= 16) and 28 000; k at the
 # edges of the register lists (8, 16, 24, 32); d below, at and between the widths
 @pytest.mark.parametrize("n,d,k,tied", [
-    (49000, 2, 8, 47940), (49000, 3, 9, 48060), (41000, 4, 16, 39960), (41001, 7, 17, 40080), (40100, 16, 32, 40080),
+    (37000, 2, 8, 35940), (37000, 3, 9, 36060), (36500, 4, 16, 35940), (36501, 7, 17, 36060), (36100, 16, 32, 36060),
+    (49000, 2, 24, 48000),
     (28100, 17, 24, 28020), (28200, 20, 25, 28020), (28300, 21, 15, 27960), (29000, 27, 10, 28980), (28500, 33, 5, 28500),
     (28500, 41, 20, 28500), (28500, 49, 30, 28500), (28500, 57, 16, 28500), (28500, 64, 32, 28440), (30000, 64, 8, 600)])
 def test_listed_queries(n, d, k, tied):
@@ -59,9 +60,9 @@ def test_listed_queries(n, d, k, tied):
     _check(x, k, idx, d2, d)
 
 
-# every point: the limits are 110 000 (d <= 3 and k > 16), 60 000 (d <= 16) and 36 000; under
+# every point: the limits are 110 000 (d <= 3 and k > 16), 50 000 (d <= 16) and 36 000; under
 # capture, where nothing may be allocated, and with a coordinate that is no number
-@pytest.mark.parametrize("n,d,k", [(110001, 1, 17), (109999, 3, 20), (60001, 3, 16), (59999, 10, 4), (60300, 15, 25),
+@pytest.mark.parametrize("n,d,k", [(110001, 1, 17), (109999, 3, 20), (50001, 3, 16), (49999, 10, 4), (50300, 15, 25),
                                    (36001, 17, 8), (35999, 27, 32), (36500, 40, 12), (36001, 64, 32)])
 @pytest.mark.parametrize("capture", [False, True])
 def test_every_point(n, d, k, capture):
